@@ -532,6 +532,8 @@ void fill_constants(sdpdem_system* s, const Sizes& z) {
   d.blk_per = z.blk_per;
   d.nablk = (int)z.ablk.size();
   d.ablk_per = z.ablk_per;
+  d.nactive = 0;
+  for (const BoxD& B : z.boxes) d.nactive += B.nact;
   d.ncells_all = (int)z.ncells_all;
   d.rncells_all = (int)z.rncells_all;
   d.have_rxn = 0;

@@ -37,8 +37,8 @@ __device__ __forceinline__ int xcd_wave() {
 // in one region of the box) lands on every XCD alike; with one chunk per
 // XCD each takes one contiguous eighth.
 template <bool ACT = false>
-__device__ __forceinline__ unsigned logical_block(const Dev& d) {
-  const unsigned b = blockIdx.x, per = (unsigned)(ACT ? d.ablk_per : d.blk_per);
+__device__ __forceinline__ unsigned logical_block(const Dev& d, unsigned b) {
+  const unsigned per = (unsigned)(ACT ? d.ablk_per : d.blk_per);
   const unsigned k = b / 8u;
   return ((k / per) * 8u + b % 8u) * per + k % per;
 }
@@ -50,9 +50,22 @@ __device__ __forceinline__ unsigned logical_block(const Dev& d) {
 // their fixed values.
 template <bool ACT = false>
 __device__ __forceinline__ int blk_box(const Dev& d, int& i) {
-  const unsigned lb = logical_block<ACT>(d);
+  const unsigned lb = logical_block<ACT>(d, blockIdx.x);
   const int2 e = ACT ? d.ablk[lb] : d.blk[lb];
   i = e.y + (int)threadIdx.x;
+  return __builtin_amdgcn_readfirstlane(e.x);
+}
+
+// The same for kernels that give each particle SPLIT lanes (launched with
+// SPLIT times the blocks): a block takes one of the SPLIT parts of a table
+// entry, an entry's parts following each other on one XCD; i0 is the part's
+// first particle.
+template <int SPLIT, bool ACT = false>
+__device__ __forceinline__ int blk_box_split(const Dev& d, int& i0) {
+  const unsigned k = blockIdx.x / 8u, b = (k / SPLIT) * 8u + blockIdx.x % 8u;
+  const unsigned lb = logical_block<ACT>(d, b);
+  const int2 e = ACT ? d.ablk[lb] : d.blk[lb];
+  i0 = e.y + (int)(k % SPLIT) * (BS / SPLIT);
   return __builtin_amdgcn_readfirstlane(e.x);
 }
 
@@ -429,6 +442,14 @@ __device__ __forceinline__ void for_stencil_pruned(const Geo& B, const Grid& G, 
       }
     }
   }
+}
+
+// orders LDS accesses of the lanes of one wave (which run them in program
+// order: only the compiler has to be held back)
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Block-wide exclusive scan of one int per thread (wave64 shuffles + LDS).

@@ -137,6 +137,7 @@ struct Dev {
   int blk_per;       // launch blocks per chunk
   const int2* ablk;  // the same over the boxes' active parts (outer walls left out)
   int nablk, ablk_per;
+  int nactive;       // particles of the boxes' active parts
   const int* rbox;   // box of every rigid slot
   // particles (current buffer)
   D4* pos;  // x, y, z, radius (lever for fluid and walls)

@@ -1,0 +1,66 @@
+"""The kernels that walk neighbour rows give a particle 16, 4 or 1 lanes by
+the size of the system; the sums are the same bits.  A box is replicated in
+one batch until the launches pass each limit: every copy (same seed, same
+particles, so the same motion and the same searches) must keep the bits the
+box gets alone."""
+import numpy as np
+import pytest
+
+from paper_2002_03120_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def S():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2002_03120_amd import sdpdem
+    sdpdem.lib()
+    return sdpdem
+
+
+def _box(kind):
+    if kind == "tank":  # walls, free surface, spheres in contact, no noise
+        p, parts, info = W.dam_break(tank=(22, 11, 18), column=(11, 11, 13), n_rigid=10, seed=4)
+        return p, W.perturb(parts, p, jitter=0.1, kT=4e-2, seed=9, spin=True), info
+    p, parts, info = W.shear_cell(15, phi=0.15, d=2.5, kBT=4e-3, shear_rate=8e-2, seed=5)
+    return p, W.perturb(parts, p, jitter=0.1, kT=None, seed=9), info
+
+
+def _state(g, n, copies, stress):
+    out = {f: g.read_field(f).reshape(copies, n, -1)
+           for f in ("POS", "VEL", "ANGVEL", "DENS", "PRES_SMOOTH", "F_SDPD", "N_SDPD", "F_CD")}
+    rows, cols = g.read_neighbors()
+    out["rowlen"] = np.diff(rows).reshape(copies, n)
+    if stress:
+        out["stress"] = g.box_stress()[1].reshape(copies, 1)
+    return out, cols
+
+
+@pytest.mark.parametrize("skin", [0.0, 0.2])
+@pytest.mark.parametrize("kind", ["tank", "shear"])
+def test_bits_do_not_depend_on_the_lanes_per_particle(S, kind, skin):
+    cell = _box(kind)
+    p, n = dict(cell[0], cell_factor=0.55, skin=skin), cell[1]["id"].shape[0]
+    assert n <= 1 << 14  # 16 lanes alone
+    ref = None
+    for total in (n, 60_000, 150_000, 300_000, 450_000):
+        copies = max(1, -(-total // n))
+        parts, boxes, box_of = W.stack_cells([cell] * copies)
+        print(f"[case] {kind} x {copies}, n={copies * n}, skin {skin}", flush=True)
+        g = S.System(p, parts, boxes=boxes, box_of=box_of)
+        g.set_stress(kind == "shear")
+        assert g.step(12) == 0
+        got, cols = _state(g, n, copies, kind == "shear")
+        if ref is None:
+            ref, ref_cols = got, cols
+            if skin:
+                assert g.info()[14] > 0  # some lists came from the candidates
+        for f, v in got.items():
+            for b in (0, copies // 2, copies - 1):
+                assert np.array_equal(v[b], ref[f][0]), (f, b)
+        assert np.array_equal(cols[:ref_cols.size], ref_cols)
+        assert np.array_equal(cols[-ref_cols.size:] - (copies - 1) * n, ref_cols)
+        g.close()
