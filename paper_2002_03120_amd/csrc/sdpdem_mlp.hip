@@ -2,10 +2,11 @@
 // bfloat16 parameters, float32 activations and float32 accumulation on the
 // matrix cores, trained with Adam.  Inference runs the hidden layers on the
 // bfloat16 matrix cores (v_mfma_f32_16x16x32_bf16, activations split into
-// three exact bfloat16 parts); a training step (forward, MSE loss,
-// backward, Adam) is one workgroup on the FP32 matrix cores
-// (v_mfma_f32_16x16x4_f32), so every reduction has a fixed order and a
-// step is bit-for-bit repeatable.
+// three exact bfloat16 parts); a training step runs forward, MSE loss and
+// backward on the FP32 matrix cores (v_mfma_f32_16x16x4_f32), a workgroup
+// per 16 rows, then adds the workgroups' gradients in order and applies
+// Adam, so every reduction has a fixed order and a step is bit-for-bit
+// repeatable.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -55,32 +56,31 @@ __device__ __forceinline__ float silu_grad(float z) {
   return s * (1.0f + z * (1.0f - s));
 }
 
-// acc += A[16 x K] B[K x 16] on the matrix cores, K a multiple of 4.  Lane
-// (r = lane % 16, q = lane / 16) supplies A(r, k0 + q) and B(k0 + q, r) per
-// step; on return it holds C(4q + v, r) in acc[v].
-template <class FA, class FB>
-__device__ __forceinline__ v4f mfma_tile(int K, FA fa, FB fb, v4f acc) {
-  const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
-  for (int k0 = 0; k0 < K; k0 += 4)
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fa(r, k0 + q), fb(k0 + q, r), acc, 0, 0, 0);
-  return acc;
-}
-
 // ---------------------------------------------------------------------------
 // inference on the bfloat16 matrix cores (v_mfma_f32_16x16x32_bf16).  The
 // parameters are bfloat16 values already; an FP32 activation is the exact
 // sum of three bfloat16 parts (its top 8 significant bits, the next 8, the
 // last 8), so three bf16 products accumulated in FP32 give the FP32
 // product, and the layer equals its FP32 evaluation up to the order of the
-// sums.  A block stages the hidden layers' weights, transposed, in LDS once
-// and its wavefronts then take groups of 16 rows in turn; each wavefront
-// keeps its 16 x 64 activation tiles in LDS.
+// sums.  A block stages the hidden layers' weights in LDS once and its
+// wavefronts then take groups of 16 rows in turn.
 
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef unsigned short v8u16 __attribute__((ext_vector_type(8)));
 
-constexpr int LDA = HID + 4;  // padded row stride of the activation tiles
 constexpr int PRED_WAVES = 4;
+
+// Where hidden weight W_{l+2}[k][j] sits in the packed copy: the operand
+// W^T of the products H_{l+2}^T = W^T H_{l+1}^T, tile by tile in the order
+// the lanes hold it (eight values, 16 bytes, per lane of tile jt, chunk c).
+// The order of a product's K index is free as long as both operands agree:
+// lane q's eight values of chunk c are the features 4q..4q+3 of the tiles 2c
+// and 2c + 1, the ones the lane's own accumulators hold after the layer
+// before, so activations go from layer to layer in registers.
+__host__ __device__ constexpr int packed_index(int l, int k, int j) {
+  const int jt = j / 16, r = j % 16, t = k / 16, q = k % 16 / 4;
+  return (((l * 4 + jt) * 2 + t / 2) * 64 + q * 16 + r) * 8 + (t % 2) * 4 + k % 4;
+}
 
 // x = hi + mid + lo exactly, each part a bfloat16 (truncations of x and of
 // the remainders: every part holds at most 8 significant bits)
@@ -95,87 +95,103 @@ __device__ __forceinline__ void split3(float x, unsigned short& h, unsigned shor
   l = (unsigned short)(__float_as_uint(r2) >> 16);
 }
 
-__global__ __launch_bounds__(64 * PRED_WAVES) void k_mlp_predict(const uint16_t* __restrict__ wq,
-                                                                 Norm nrm,
-                                                                 const float* __restrict__ x,
-                                                                 float* __restrict__ y, int64_t n,
-                                                                 int64_t groups_per_wave) {
-  // W2^T and W3^T: wt[l][j * HID + k] = W_{l+2}[k][j] (bf16 bits)
-  __shared__ __attribute__((aligned(16))) unsigned short wt[2][HID * HID];
-  __shared__ float w1[4 * HID], bias[3][HID], w4[HID + 1];
-  __shared__ float act[PRED_WAVES][2][16 * LDA];
+// A wavefront takes 16 rows at a time, transposed: lane (r, q) holds the
+// features 4q..4q+3 of every 16-feature tile of row r.  Bound by the vector
+// ALU (192 sigmoids a row, two quarter-rate instructions each, and the
+// splits); the weights come from LDS in operand order, the activations stay
+// in registers.  With the activations passing through LDS between layers and
+// the weights transposed into LDS by every block it took 117 us for 2^20
+// rows and 10.4 us for 64; now 81 and 3.7 us.
+__global__ __launch_bounds__(64 * PRED_WAVES) void k_mlp_predict(
+    const uint16_t* __restrict__ wq, const uint16_t* __restrict__ wpk, Norm nrm,
+    const float* __restrict__ x, float* __restrict__ y, int64_t n, int64_t groups_per_wave) {
+  __shared__ __attribute__((aligned(16))) unsigned short wt[2 * HID * HID];
+  __shared__ __attribute__((aligned(16))) float bias[3][HID], w4[HID];
   const int tid = threadIdx.x;
-  for (int e = tid; e < 2 * HID * HID; e += 64 * PRED_WAVES) {
-    const int l = e / (HID * HID), rem = e % (HID * HID), k = rem / HID, j = rem % HID;
-    wt[l][j * HID + k] = wq[OW[l + 1] + k * HID + j];
-  }
-  for (int e = tid; e < 4 * HID; e += 64 * PRED_WAVES) w1[e] = bf16_to_f32(wq[OW1 + e]);
-  for (int e = tid; e < 3 * HID; e += 64 * PRED_WAVES)
-    bias[e / HID][e % HID] = bf16_to_f32(wq[OB[e / HID] + e % HID]);
-  for (int e = tid; e <= HID; e += 64 * PRED_WAVES) w4[e] = bf16_to_f32(wq[OW4 + e]);
-  __syncthreads();
+#pragma unroll
+  for (int e = 8 * tid; e < 2 * HID * HID; e += 8 * 64 * PRED_WAVES)
+    *reinterpret_cast<v8u16*>(wt + e) = *reinterpret_cast<const v8u16*>(wpk + e);
+  if (tid < 3 * HID) bias[tid / HID][tid % HID] = bf16_to_f32(wq[OB[tid / HID] + tid % HID]);
+  if (tid >= 3 * HID) w4[tid - 3 * HID] = bf16_to_f32(wq[OW4 + tid - 3 * HID]);
   const int w = tid >> 6, lane = tid & 63, r = lane & 15, q = lane >> 4;
-  float* h0 = act[w][0];
-  float* h1 = act[w][1];
+  float w1[4];
+#pragma unroll
+  for (int jt = 0; jt < 4; ++jt) w1[jt] = bf16_to_f32(wq[OW1 + q * HID + 16 * jt + r]);
+  const float b4 = bf16_to_f32(wq[OB4]);
+  const float mean = q == 0 ? nrm.mean[0] : q == 1 ? nrm.mean[1] : q == 2 ? nrm.mean[2]
+                                                                          : nrm.mean[3];
+  const float inv = q == 0 ? nrm.inv_std[0] : q == 1 ? nrm.inv_std[1] : q == 2 ? nrm.inv_std[2]
+                                                                              : nrm.inv_std[3];
   const int64_t wave = (int64_t)blockIdx.x * PRED_WAVES + w;
   const int64_t nwaves = (int64_t)gridDim.x * PRED_WAVES;
+  const int64_t first = wave * 16 + r;
+  float xin = first < n ? x[first * 4 + q] : mean;
+  __syncthreads();
   for (int64_t it = 0; it < groups_per_wave; ++it) {
-    const int64_t row0 = (wave + it * nwaves) * 16;
-    if (row0 >= n) break;  // a wavefront's own loop: no block barrier inside
-    // layer 1: K = 4 features, one FP32 MFMA per 16 x 16 tile
-    {
-      const int64_t row = row0 + r;
-      const float a = row < n ? (x[row * 4 + q] - nrm.mean[q]) * nrm.inv_std[q] : 0.0f;
-      for (int jt = 0; jt < 4; ++jt) {
-        const float b0 = bias[0][16 * jt + r];
-        v4f acc = {b0, b0, b0, b0};
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, w1[q * HID + 16 * jt + r], acc, 0, 0, 0);
-        for (int v = 0; v < 4; ++v) h0[(4 * q + v) * LDA + 16 * jt + r] = silu(acc[v]);
-      }
+    const int64_t row = (wave + it * nwaves) * 16 + r;
+    if (row - r >= n) break;  // a wavefront's own loop: no block barrier inside
+    const float xb = (xin - mean) * inv;
+    const int64_t next = row + nwaves * 16;  // in flight while this group is evaluated
+    xin = next < n ? x[next * 4 + q] : mean;
+    // layer 1: K = 4 features, one FP32 MFMA per tile
+    v4f h[4];
+#pragma unroll
+    for (int jt = 0; jt < 4; ++jt) {
+      v4f acc = *reinterpret_cast<const v4f*>(&bias[0][16 * jt + 4 * q]);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[jt], xb, acc, 0, 0, 0);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) h[jt][v] = silu(acc[v]);
     }
-    // layers 2 and 3: K = 64 as two chunks of 32; lane (r, q) supplies
-    // A(r, 32c + 8q .. + 7) and B(32c + 8q .. + 7, r), holds C(4q + v, r)
+    // layers 2 and 3: K = 64 as two chunks of 32
+#pragma unroll
     for (int l = 0; l < 2; ++l) {
-      const float* hin = l == 0 ? h0 : h1;
-      float* hout = l == 0 ? h1 : h0;
       v8u16 ah[2], am[2], al[2];
+#pragma unroll
       for (int c = 0; c < 2; ++c)
+#pragma unroll
         for (int e = 0; e < 8; ++e) {
           unsigned short hh, mm, ll;
-          split3(hin[r * LDA + 32 * c + 8 * q + e], hh, mm, ll);
+          split3(h[2 * c + e / 4][e % 4], hh, mm, ll);
           ah[c][e] = hh;
           am[c][e] = mm;
           al[c][e] = ll;
         }
+#pragma unroll
       for (int jt = 0; jt < 4; ++jt) {
-        const float bj = bias[l + 1][16 * jt + r];
-        v4f acc = {bj, bj, bj, bj};
+        v4f acc = *reinterpret_cast<const v4f*>(&bias[l + 1][16 * jt + 4 * q]);
+#pragma unroll
         for (int c = 0; c < 2; ++c) {
-          const v8u16 bw =
-              *reinterpret_cast<const v8u16*>(&wt[l][(16 * jt + r) * HID + 32 * c + 8 * q]);
-          const v8bf b = __builtin_bit_cast(v8bf, bw);
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, ah[c]), b, acc,
+          const v8bf wv = __builtin_bit_cast(
+              v8bf, *reinterpret_cast<const v8u16*>(wt + (((l * 4 + jt) * 2 + c) * 64 + lane) * 8));
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv, __builtin_bit_cast(v8bf, ah[c]), acc,
                                                         0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, am[c]), b, acc,
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv, __builtin_bit_cast(v8bf, am[c]), acc,
                                                         0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, al[c]), b, acc,
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv, __builtin_bit_cast(v8bf, al[c]), acc,
                                                         0, 0, 0);
         }
-        for (int v = 0; v < 4; ++v) hout[(4 * q + v) * LDA + 16 * jt + r] = silu(acc[v]);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) h[jt][v] = silu(acc[v]);
       }
     }
-    // output layer: lanes (r, q) sum k in [16q, 16q + 16), then across q
+    // output layer: this lane's 16 features, then across q
     float p = 0.0f;
-    for (int k = 16 * q; k < 16 * q + 16; ++k) p += h0[r * LDA + k] * w4[k];
+#pragma unroll
+    for (int jt = 0; jt < 4; ++jt) {
+      const v4f wo = *reinterpret_cast<const v4f*>(&w4[16 * jt + 4 * q]);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) p += h[jt][v] * wo[v];
+    }
     p += __shfl_xor(p, 16, 64);
     p += __shfl_xor(p, 32, 64);
-    const int64_t row = row0 + r;
-    if (q == 0 && row < n) y[row] = p + w4[HID];
+    if (q == 0 && row < n) y[row] = p + b4;
   }
 }
 
 // ---------------------------------------------------------------------------
-// training step: one workgroup of 4 wavefronts
+// training step: a workgroup per 16 rows of the batch, then the update
+
+constexpr int GROUPS = MAXB / 16;
 
 struct Train {
   float* master;
@@ -183,153 +199,199 @@ struct Train {
   float* v;
   float* grad;
   uint16_t* wq;
+  uint16_t* wpk;  // hidden weights again, in the order of packed_index
   float* loss;
-  float* xn;   // [MAXB x 4]
-  float* z;    // [3][MAXB x 64]
-  float* h;    // [3][MAXB x 64]
-  float* dz0;  // [MAXB x 64]
-  float* dz1;  // [MAXB x 64]
-  float* dy;   // [MAXB]
+  float* part;   // [GROUPS][NP]: every group's share of the gradient
+  float* lpart;  // [GROUPS]: its sum of squared residuals
 };
 
-__global__ __launch_bounds__(256) void k_mlp_train(Train T, Norm nrm, const float* __restrict__ x,
-                                                   const float* __restrict__ t, int B, int update,
-                                                   float lr, float b1, float b2, float eps,
-                                                   float bc1, float bc2) {
-  __shared__ float red[256];
+// acc += A[16 x K] B[K x 16] on the FP32 matrix cores.  Lane (r = lane % 16,
+// q = lane / 16) supplies A(r, k0 + q) and B(k0 + q, r) per step; on return
+// it holds C(4q + v, r) in acc[v].
+template <int K, class FA, class FB>
+__device__ __forceinline__ v4f mfma_tile(FA fa, FB fb, v4f acc) {
+  const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
+#pragma unroll
+  for (int k0 = 0; k0 < K; k0 += 4)
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fa(r, k0 + q), fb(k0 + q, r), acc, 0, 0, 0);
+  return acc;
+}
+
+// LDS row strides: 68 floats keep the 16 x 4 lanes of an operand read of an
+// activation tile on 64 different banks, 84 bfloat16 words the reads of the
+// weights along either index at two lanes per bank
+constexpr int LDA = HID + 4, LDW = 84;
+
+// Forward and backward of 16 rows and their share of the gradient (rows past
+// the batch contribute nothing).  Every intermediate stays in LDS.  Bound by
+// latency: a chain of five layers of 16 dependent MFMAs and their LDS reads.
+// One workgroup for the whole batch of 256, its activations in global memory,
+// took 370 us; this takes one sixteenth of the chain per workgroup.
+__global__ __launch_bounds__(256) void k_mlp_grad(Train T, Norm nrm, const float* __restrict__ x,
+                                                  const float* __restrict__ t, int B) {
+  __shared__ __attribute__((aligned(16))) uint16_t ws[2][HID * LDW];  // W2, W3
+  __shared__ float xn[16 * 4], act[3][16 * LDA], slope[3][16 * LDA], dzb[2][16 * LDA];
+  __shared__ float dy[16], sq[16], w4[HID];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r = lane & 15, q = lane >> 4;
-  const int Bp = (B + 15) & ~15;
-  const int ngroups = Bp / 16;
-  // inputs, normalised; padding rows are zero
-  for (int k = tid; k < Bp * 4; k += 256) {
-    const int i = k >> 2, f = k & 3;
-    T.xn[k] = i < B ? (x[k] - nrm.mean[f]) * nrm.inv_std[f] : 0.0f;
+  const int row0 = 16 * (int)blockIdx.x;
+  float* const part = T.part + (size_t)blockIdx.x * NP;
+#pragma unroll
+  for (int e = tid; e < 2 * HID * HID / 8; e += 256) {
+    const int l = e / (HID * HID / 8), o = 8 * (e % (HID * HID / 8));
+    const v8u16 v = *reinterpret_cast<const v8u16*>(T.wq + OW[l + 1] + o);
+    uint16_t* const to = &ws[l][o / HID * LDW + o % HID];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) to[u] = v[u];
   }
-  __syncthreads();
-  // forward: z_l = h_{l-1} W_l + b_l, h_l = silu(z_l)
+  if (tid < HID) w4[tid] = bf16_to_f32(T.wq[OW4 + tid]);
+  const float xv = row0 + r < B ? (x[(row0 + r) * 4 + q] - nrm.mean[q]) * nrm.inv_std[q] : 0.0f;
+  if (w == 0) xn[r * 4 + q] = xv;
+  const int j = 16 * w + r;  // wave w computes the features 16 w .. of every layer
+  // forward: z_l = h_{l-1} W_l + b_l, h_l = silu(z_l), and silu'(z_l)
+#pragma unroll
   for (int l = 0; l < 3; ++l) {
-    const int K = l == 0 ? 4 : HID;
-    const float* hin = l == 0 ? T.xn : T.h + (size_t)(l - 1) * MAXB * HID;
-    float* zl = T.z + (size_t)l * MAXB * HID;
-    float* hl = T.h + (size_t)l * MAXB * HID;
-    for (int item = w; item < ngroups * 4; item += 4) {
-      const int g = item >> 2, jt = item & 3;
-      const float bias = bf16_to_f32(T.wq[OB[l] + 16 * jt + r]);
-      v4f acc = {bias, bias, bias, bias};
-      acc = mfma_tile(
-          K, [&](int i, int k) { return hin[(16 * g + i) * K + k]; },
-          [&](int k, int j) { return bf16_to_f32(T.wq[OW[l] + k * HID + 16 * jt + j]); }, acc);
-      for (int v = 0; v < 4; ++v) {
-        const int idx = (16 * g + 4 * q + v) * HID + 16 * jt + r;
-        zl[idx] = acc[v];
-        hl[idx] = silu(acc[v]);
-      }
+    const float bj = bf16_to_f32(T.wq[OB[l] + j]);
+    v4f acc = {bj, bj, bj, bj};
+    if (l == 0) {
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xv, bf16_to_f32(T.wq[OW1 + q * HID + j]), acc, 0,
+                                                 0, 0);
+    } else {
+      const float* hin = act[l - 1];
+      const uint16_t* wl = ws[l - 1];
+      acc = mfma_tile<HID>([&](int i, int k) { return hin[i * LDA + k]; },
+                           [&](int k, int) { return bf16_to_f32(wl[k * LDW + j]); }, acc);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      act[l][(4 * q + v) * LDA + j] = silu(acc[v]);
+      slope[l][(4 * q + v) * LDA + j] = silu_grad(acc[v]);
     }
     __syncthreads();
   }
-  // output, residual, dL/dy = 2 (y - t) / B and the loss
-  const float* h3 = T.h + (size_t)2 * MAXB * HID;
-  float part = 0.0f;
-  for (int i = tid; i < Bp; i += 256) {
-    float y = bf16_to_f32(T.wq[OB4]);
-    for (int k = 0; k < HID; ++k) y += h3[i * HID + k] * bf16_to_f32(T.wq[OW4 + k]);
-    const float res = i < B ? y - t[i] : 0.0f;
-    T.dy[i] = 2.0f * res / (float)B;
-    part += res * res;
+  // output and dL/dy = 2 (y - t) / B: 16 lanes per row
+  {
+    const int i = tid >> 4, c = tid & 15;
+    float y = 0.0f;
+#pragma unroll
+    for (int m = 0; m < HID; m += 16) y += act[2][i * LDA + c + m] * w4[c + m];
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) y += __shfl_xor(y, o, 16);
+    if (c == 0) {
+      const float res = row0 + i < B ? y + bf16_to_f32(T.wq[OB4]) - t[row0 + i] : 0.0f;
+      dy[i] = 2.0f * res / (float)B;
+      sq[i] = res * res;
+    }
   }
-  red[tid] = part;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (tid < o) red[tid] += red[tid + o];
-    __syncthreads();
-  }
-  if (tid == 0) T.loss[0] = red[0] / (float)B;
   // output layer gradients and dz_3 = (dy W4^T) * silu'(z_3)
   if (tid < HID) {
     float s = 0.0f;
-    for (int i = 0; i < Bp; ++i) s += h3[i * HID + tid] * T.dy[i];
-    T.grad[OW4 + tid] = s;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s += act[2][i * LDA + tid] * dy[i];
+    part[OW4 + tid] = s;
   } else if (tid == HID) {
-    float s = 0.0f;
-    for (int i = 0; i < Bp; ++i) s += T.dy[i];
-    T.grad[OB4] = s;
-  }
-  {
-    const float* z3 = T.z + (size_t)2 * MAXB * HID;
-    for (int k = tid; k < Bp * HID; k += 256) {
-      const int i = k / HID, c = k % HID;
-      T.dz0[k] = T.dy[i] * bf16_to_f32(T.wq[OW4 + c]) * silu_grad(z3[k]);
+    float s = 0.0f, l2 = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      s += dy[i];
+      l2 += sq[i];
     }
+    part[OB4] = s;
+    T.lpart[blockIdx.x] = l2;
+  }
+#pragma unroll
+  for (int e = tid; e < 16 * HID; e += 256) {
+    const int i = e / HID, c = e % HID;
+    dzb[0][i * LDA + c] = dy[i] * w4[c] * slope[2][i * LDA + c];
   }
   __syncthreads();
-  float* dz = T.dz0;
-  float* dzn = T.dz1;
+#pragma unroll
   for (int l = 2; l >= 0; --l) {
-    const int K = l == 0 ? 4 : HID;  // fan-in of layer l
-    const float* hin = l == 0 ? T.xn : T.h + (size_t)(l - 1) * MAXB * HID;
-    // grad W_l = h_{l-1}^T dz_l  [K x 64], contraction over the batch
-    const int nti = l == 0 ? 1 : 4;
-    for (int item = w; item < nti * 4; item += 4) {
-      const int ti = item >> 2, tj = item & 3;
+    const float* dz = dzb[l & 1];  // layer 3 (l = 2) and layer 1 in the first
+    float* dzn = dzb[(l & 1) ^ 1];
+    if (l > 0) {
+      // dz_{l-1} = (dz_l W_l^T) * silu'(z_{l-1})
+      const uint16_t* wl = ws[l - 1];
       v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
-      acc = mfma_tile(
-          Bp,
+      acc = mfma_tile<HID>([&](int i, int k) { return dz[i * LDA + k]; },
+                           [&](int k, int) { return bf16_to_f32(wl[j * LDW + k]); }, acc);
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        dzn[(4 * q + v) * LDA + j] = acc[v] * slope[l - 1][(4 * q + v) * LDA + j];
+    }
+    // grad W_l = h_{l-1}^T dz_l: this wave's columns, contraction over the rows
+#pragma unroll
+    for (int ti = 0; ti < (l == 0 ? 1 : 4); ++ti) {
+      v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
+      acc = mfma_tile<16>(
           [&](int i, int k) {
-            const int a = 16 * ti + i;
-            return a < K ? hin[k * K + a] : 0.0f;
+            return l == 0 ? (i < 4 ? xn[k * 4 + (i & 3)] : 0.0f)
+                          : act[l == 0 ? 0 : l - 1][k * LDA + 16 * ti + i];
           },
-          [&](int k, int j) { return dz[k * HID + 16 * tj + j]; }, acc);
+          [&](int k, int) { return dz[k * LDA + j]; }, acc);
+#pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int a = 16 * ti + 4 * q + v;
-        if (a < K) T.grad[OW[l] + a * HID + 16 * tj + r] = acc[v];
+        if (l > 0 || a < 4) part[OW[l] + a * HID + j] = acc[v];
       }
     }
     if (tid < HID) {
       float s = 0.0f;
-      for (int i = 0; i < Bp; ++i) s += dz[i * HID + tid];
-      T.grad[OB[l] + tid] = s;
-    }
-    if (l > 0) {
-      // dz_{l-1} = (dz_l W_l^T) * silu'(z_{l-1})
-      const float* zp = T.z + (size_t)(l - 1) * MAXB * HID;
-      for (int item = w; item < ngroups * 4; item += 4) {
-        const int g = item >> 2, jt = item & 3;
-        v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
-        acc = mfma_tile(
-            HID, [&](int i, int k) { return dz[(16 * g + i) * HID + k]; },
-            [&](int k, int j) { return bf16_to_f32(T.wq[OW[l] + (16 * jt + j) * HID + k]); }, acc);
-        for (int v = 0; v < 4; ++v) {
-          const int idx = (16 * g + 4 * q + v) * HID + 16 * jt + r;
-          dzn[idx] = acc[v] * silu_grad(zp[idx]);
-        }
-      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s += dz[i * LDA + tid];
+      part[OB[l] + tid] = s;
     }
     __syncthreads();
-    float* tmp = dz;
-    dz = dzn;
-    dzn = tmp;
-  }
-  if (!update) return;
-  // Adam with bias correction on the float32 masters, then the bf16 copy
-  for (int p = tid; p < NP; p += 256) {
-    const float g = T.grad[p];
-    const float m = b1 * T.m[p] + (1.0f - b1) * g;
-    const float v = b2 * T.v[p] + (1.0f - b2) * g * g;
-    T.m[p] = m;
-    T.v[p] = v;
-    const float mh = m / bc1, vh = v / bc2;
-    const float nw = T.master[p] - lr * mh / (sqrtf(vh) + eps);
-    T.master[p] = nw;
-    T.wq[p] = f32_to_bf16(nw);
   }
 }
 
-__global__ void k_mlp_init(float* master, uint16_t* wq, float* m, float* v, int np) {
-  int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= np) return;
-  wq[p] = f32_to_bf16(master[p]);
-  m[p] = 0.0f;
-  v[p] = 0.0f;
+// every parameter's bfloat16 copy, in both layouts
+__device__ __forceinline__ void store_used(const Train& T, int p, float master) {
+  const uint16_t b = f32_to_bf16(master);
+  T.wq[p] = b;
+#pragma unroll
+  for (int l = 0; l < 2; ++l) {
+    const int o = p - OW[l + 1];
+    if (o >= 0 && o < HID * HID) T.wpk[packed_index(l, o / HID, o % HID)] = b;
+  }
+}
+
+// the groups' shares added in order (bit-for-bit repeatable), then Adam with
+// bias correction on the float32 masters and the bfloat16 copies
+__global__ __launch_bounds__(256) void k_mlp_update(Train T, int B, int update, float lr, float b1,
+                                                    float b2, float eps, float bc1, float bc2) {
+  const int p = blockIdx.x * 256 + threadIdx.x;
+  const int ng = (B + 15) / 16;
+  if (p == 0) {
+    float s = 0.0f;
+    for (int k = 0; k < ng; ++k) s += T.lpart[k];
+    T.loss[0] = s / (float)B;
+  }
+  if (p >= NP) return;
+  float pk[GROUPS];
+#pragma unroll
+  for (int k = 0; k < GROUPS; ++k) pk[k] = k < ng ? T.part[(size_t)k * NP + p] : 0.0f;
+  float g = 0.0f;
+#pragma unroll
+  for (int k = 0; k < GROUPS; ++k) g += pk[k];
+  T.grad[p] = g;
+  if (!update) return;
+  const float m = b1 * T.m[p] + (1.0f - b1) * g;
+  const float v = b2 * T.v[p] + (1.0f - b2) * g * g;
+  T.m[p] = m;
+  T.v[p] = v;
+  const float mh = m / bc1, vh = v / bc2;
+  const float nw = T.master[p] - lr * mh / (sqrtf(vh) + eps);
+  T.master[p] = nw;
+  store_used(T, p, nw);
+}
+
+__global__ void k_mlp_init(Train T) {
+  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= NP) return;
+  store_used(T, p, T.master[p]);
+  T.m[p] = 0.0f;
+  T.v[p] = 0.0f;
 }
 
 struct Bump {
@@ -352,13 +414,10 @@ size_t mlp_layout(char* base, Train* T) {
   t.v = b.take<float>(NP);
   t.grad = b.take<float>(NP);
   t.wq = b.take<uint16_t>(NP);
+  t.wpk = b.take<uint16_t>(2 * HID * HID);
   t.loss = b.take<float>(1);
-  t.xn = b.take<float>((size_t)MAXB * 4);
-  t.z = b.take<float>((size_t)3 * MAXB * HID);
-  t.h = b.take<float>((size_t)3 * MAXB * HID);
-  t.dz0 = b.take<float>((size_t)MAXB * HID);
-  t.dz1 = b.take<float>((size_t)MAXB * HID);
-  t.dy = b.take<float>(MAXB);
+  t.part = b.take<float>((size_t)GROUPS * NP);
+  t.lpart = b.take<float>(GROUPS);
   if (T) *T = t;
   return b.off + 256;
 }
@@ -412,7 +471,7 @@ int sdpdem_mlp_create(const sdpdem_mlp_config* cfg, const float* init_params, vo
                            st) == hipSuccess;
   ok = ok && hipStreamSynchronize(st) == hipSuccess;
   if (ok) {
-    k_mlp_init<<<(NP + 255) / 256, 256, 0, st>>>(m->T.master, m->T.wq, m->T.m, m->T.v, NP);
+    k_mlp_init<<<(NP + 255) / 256, 256, 0, st>>>(m->T);
     ok = hipStreamSynchronize(st) == hipSuccess && hipGetLastError() == hipSuccess;
   }
   if (!ok) {
@@ -431,7 +490,7 @@ int sdpdem_mlp_predict(sdpdem_mlp* m, const float* d_x, float* d_y, int64_t n, v
   const int64_t blocks = std::min<int64_t>((groups + PRED_WAVES - 1) / PRED_WAVES, 2048);
   const int64_t per_wave = (groups + blocks * PRED_WAVES - 1) / (blocks * PRED_WAVES);
   k_mlp_predict<<<(unsigned)blocks, 64 * PRED_WAVES, 0, (hipStream_t)hip_stream>>>(
-      m->T.wq, m->nrm, d_x, d_y, n, per_wave);
+      m->T.wq, m->T.wpk, m->nrm, d_x, d_y, n, per_wave);
   return hipGetLastError() == hipSuccess ? SDPDEM_OK : SDPDEM_E_HIP;
 }
 
@@ -444,9 +503,10 @@ int sdpdem_mlp_train_step(sdpdem_mlp* m, const float* d_x, const float* d_t, int
     bc1 = (float)(1.0 - std::pow((double)m->cfg.beta1, (double)m->steps));
     bc2 = (float)(1.0 - std::pow((double)m->cfg.beta2, (double)m->steps));
   }
-  k_mlp_train<<<1, 256, 0, (hipStream_t)hip_stream>>>(m->T, m->nrm, d_x, d_t, batch, update ? 1 : 0,
-                                                     m->cfg.lr, m->cfg.beta1, m->cfg.beta2,
-                                                     m->cfg.eps, bc1, bc2);
+  hipStream_t st = (hipStream_t)hip_stream;
+  k_mlp_grad<<<(unsigned)((batch + 15) / 16), 256, 0, st>>>(m->T, m->nrm, d_x, d_t, batch);
+  k_mlp_update<<<(NP + 255) / 256, 256, 0, st>>>(m->T, batch, update ? 1 : 0, m->cfg.lr,
+                                                 m->cfg.beta1, m->cfg.beta2, m->cfg.eps, bc1, bc2);
   return hipGetLastError() == hipSuccess ? SDPDEM_OK : SDPDEM_E_HIP;
 }
 
