@@ -452,6 +452,20 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// 16 bytes per lane from global memory straight into LDS, lane k's to
+// l + 16 k (l uniform over the wave); the waits keep the compiler from moving LDS
+// reads across them
+__device__ __forceinline__ void load_to_lds16(const void* g, void* l) {
+  __builtin_amdgcn_global_load_lds(
+      (__attribute__((address_space(1))) void*)const_cast<void*>(g),
+      (__attribute__((address_space(3))) void*)l, 16, 0, 0);
+}
+__device__ __forceinline__ void wait_loads() {
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+  asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
 // Block-wide exclusive scan of one int per thread (wave64 shuffles + LDS).
 __device__ inline int block_exclusive_scan(int v, int* lds, int* total) {
   int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -479,6 +493,31 @@ __device__ inline int block_exclusive_scan(int v, int* lds, int* total) {
   return res;
 }
 
+// a ^ b ^ c in one instruction (the compiler emits two)
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
+// square root of x >= 0 (0 below the smallest normal number) from the
+// hardware reciprocal square root and one correction of the residual: half
+// the instructions of the library call, which also scales subnormals
+__device__ __forceinline__ float sqrtf_nr(float x) {
+  const float y = __builtin_amdgcn_rsqf(x);
+  const float s = x * y;
+  const float r = __builtin_fmaf(__builtin_fmaf(-s, s, x), 0.5f * y, s);
+  return x >= 1.17549435e-38f ? r : 0.0f;
+}
+
+// -2 ln(u) for u in [2^-24, 1] from the hardware log2, the product with
+// -2 ln 2 carried to twice the precision
+__device__ __forceinline__ float minus_2_log(float u) {
+  constexpr float hi = -1.3862943611198906f;
+  constexpr float lo = (float)(-1.3862943611198906188 - (double)hi);
+  const float l = __builtin_amdgcn_logf(u);
+  const float t = l * hi;
+  return t + __builtin_fmaf(l, lo, __builtin_fmaf(l, hi, -t));
+}
+
 // Philox4x32-10 (Salmon et al., SC'11): two 32x32 -> 64-bit products per
 // round with the published multipliers, Weyl key increments between rounds.
 __device__ __forceinline__ void philox10(uint32_t& c0, uint32_t& c1, uint32_t& c2, uint32_t& c3,
@@ -489,8 +528,7 @@ __device__ __forceinline__ void philox10(uint32_t& c0, uint32_t& c1, uint32_t& c
     const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
     const uint32_t hi0 = (uint32_t)(p0 >> 32), lo0 = (uint32_t)p0;
     const uint32_t hi1 = (uint32_t)(p1 >> 32), lo1 = (uint32_t)p1;
-    uint32_t n0 = hi1 ^ c1 ^ k0;
-    uint32_t n2 = hi0 ^ c3 ^ k1;
+    const uint32_t n0 = xor3(hi1, c1, k0), n2 = xor3(hi0, c3, k1);
     c0 = n0;
     c1 = lo1;
     c2 = n2;
@@ -514,7 +552,7 @@ __device__ __forceinline__ void pair_normals(uint32_t a, uint32_t b, uint32_t st
   const float u[4] = {u01(c0), u01(c1), u01(c2), u01(c3)};
 #pragma unroll
   for (int m = 0; m < 2; ++m) {
-    float rad = sqrtf(-2.0f * logf(u[2 * m]));
+    const float rad = sqrtf_nr(minus_2_log(u[2 * m]));
     // sin and cos of 2 pi u by the hardware units, whose argument is in
     // revolutions (largest error 1.3e-7 over every u this generator makes)
     const float cs = __builtin_amdgcn_cosf(u[2 * m + 1]), sn = __builtin_amdgcn_sinf(u[2 * m + 1]);

@@ -644,13 +644,15 @@ void launch_smooth(const Dev& d, bool all, hipStream_t st) {
 struct PairCtx {
   Geo G;
   uint32_t ib, gi;  // box's first id, box-local noise index of i
-  float jump, kT;
+  float jump;
+  float across, along;  // thermal amplitudes over sqrt(F / (d_i d_j))
   bool le, noise;
   uint32_t key0, key1, step;
 };
 
 template <bool NOISE>
 __device__ __forceinline__ PairCtx pair_ctx(const Dev& d, const BoxD& B, const PR& ri) {
+#pragma clang fp contract(off)
   PairCtx c;
   c.ib = B.id_base;
   c.gi = (uint32_t)ri.gid - c.ib;
@@ -658,7 +660,10 @@ __device__ __forceinline__ PairCtx pair_ctx(const Dev& d, const BoxD& B, const P
   c.le = c.G.le;
   c.jump = (float)c.G.le_jump;
   c.noise = NOISE && B.noise;
-  c.kT = B.kTf;
+  // sa sqrt(1/2) and sqrt(2/3 sa^2 + 1/3 sb^2), sa^2 = 4 kT C_A F / (d_i d_j)
+  const float cn = d.cT * d.inv_sqrt_dtf, kT4 = 4.0f * B.kTf;
+  c.across = NOISE ? cn * sqrtf(0.5f * kT4 * d.CAf) : 0.0f;
+  c.along = NOISE ? cn * sqrtf(kT4 * (d.CAf * (2.0f / 3.0f) + d.CBf * (1.0f / 3.0f))) : 0.0f;
   c.key0 = B.key0;
   c.key1 = B.key1;
   c.step = NOISE ? (uint32_t)d.dstep[0] : 0u;  // noise counter
@@ -666,23 +671,25 @@ __device__ __forceinline__ PairCtx pair_ctx(const Dev& d, const BoxD& B, const P
 }
 
 // the pair force of partner j on i: [0..2] F, [3..5] torque without its
-// lever, [6..8] F^C + F^D, [9] virial share
+// lever, [6..8] F^C + F^D, [9] virial share.  Fused operations are written
+// out, so that every kernel that calls this rounds alike.
 enum { PT_N = 10 };
 
 template <bool NOISE, bool STRESS>
 __device__ __forceinline__ void pair_terms(const Dev& d, const PairCtx& c, const PR& ri,
                                            const PR& rj, float out[PT_N]) {
+#pragma clang fp contract(off)
+  const auto fma = [](float x, float y, float z) { return __builtin_fmaf(x, y, z); };
   double dx_ = ri.x - rj.x, dy_ = ri.y - rj.y, dz_ = ri.z - rj.z;
   const int kz = NOISE ? min_img_fast(c.G, dx_, dy_, dz_) : min_img_box(c.G, dx_, dy_, dz_);
-  const double r2d = dx_ * dx_ + dy_ * dy_ + dz_ * dz_;
+  const double r2d = __builtin_fma(dz_, dz_, __builtin_fma(dx_, dx_, dy_ * dy_));
   const float rx = (float)dx_, ry = (float)dy_, rz = (float)dz_;
-  const float inv_r = __builtin_amdgcn_rsqf((float)r2d);
-  const float r = (float)r2d * inv_r;
+  const float r2f = (float)r2d, inv_r = __builtin_amdgcn_rsqf(r2f);
   const float ex = rx * inv_r, ey = ry * inv_r, ez = rz * inv_r;
   // 1 - r/h = (h^2 - r^2) / (h (h + r)), the difference taken in FP64 so
   // that pairs close to the cut-off keep full FP32 relative precision
-  const float omq =
-      fmaxf((float)(d.h2 - r2d) * d.inv_hf * __builtin_amdgcn_rcpf(d.hf + r), 0.0f);
+  const float omq = fmaxf(
+      (float)(d.h2 - r2d) * d.inv_hf * __builtin_amdgcn_rcpf(fma(r2f, inv_r, d.hf)), 0.0f);
   const float Fk = d.cFf * omq * omq;  // F(r) = -W'(r)/r, Eq. F
   // Pair force = along-e part + transverse part.  The torque takes the
   // transverse part only (e x e = 0), which keeps the FP32 cross product
@@ -695,25 +702,21 @@ __device__ __forceinline__ void pair_terms(const Dev& d, const PairCtx& c, const
   // dissipative force, Eq. FijD: -ga v_ij - (ga + 2 gb)/3 (e.v_ij) e; a
   // partner seen through a sheared z face moves with its image velocity
   float vx = ri.vx - rj.vx;
-  if (c.le) vx = vx - (float)kz * c.jump;
+  if (c.le) vx = fma(-(float)kz, c.jump, vx);
   const float vy = ri.vy - rj.vy, vz = ri.vz - rj.vz;
-  const float ev = ex * vx + ey * vy + ez * vz;
+  const float ev = fma(ez, vz, fma(ex, vx, ey * vy));
   const float cde = d.kBf * fdd * ev;
   const float cdv = d.kAf * fdd;
-  float tx = cdv * vx, ty = cdv * vy, tz = cdv * vz;
-  const float cx_ = pc * rx + cde * ex + tx;
-  const float cy_ = pc * ry + cde * ey + ty;
-  const float cz_ = pc * rz + cde * ez + tz;
+  const float cx_ = fma(cdv, vx, fma(pc, rx, cde * ex));
+  const float cy_ = fma(cdv, vy, fma(pc, ry, cde * ey));
+  const float cz_ = fma(cdv, vz, fma(pc, rz, cde * ez));
   // rotational force, Eq. FijR: -gamma^a (r_ij / 2) x (w_i + w_j)
   const float sx = ri.wx + rj.wx, sy = ri.wy + rj.wy, sz = ri.wz + rj.wz;
   const float gr = d.kRf * fdd;
-  const float rrx = gr * (ry * sz - rz * sy);
-  const float rry = gr * (rz * sx - rx * sz);
-  const float rrz = gr * (rx * sy - ry * sx);
-  float fx = cx_ + rrx, fy = cy_ + rry, fz = cz_ + rrz;
-  tx += rrx;
-  ty += rry;
-  tz += rrz;
+  const float qx = fma(ry, sz, -(rz * sy)), qy = fma(rz, sx, -(rx * sz)),
+              qz = fma(rx, sy, -(ry * sx));
+  float fx = fma(gr, qx, cx_), fy = fma(gr, qy, cy_), fz = fma(gr, qz, cz_);
+  float tx = fma(cdv, vx, gr * qx), ty = fma(cdv, vy, gr * qy), tz = fma(cdv, vz, gr * qz);
   if (c.noise) {
     // thermal force, Eq. FijT: (sa dW^S + sb tr(dW)/3 1) e for a matrix
     // of independent increments is Gaussian with variance 1/2 across e
@@ -723,27 +726,26 @@ __device__ __forceinline__ void pair_terms(const Dev& d, const PairCtx& c, const
     float z[4];
     const uint32_t gi = c.gi, gj = (uint32_t)rj.gid - c.ib;
     pair_normals(gi, gj, c.step, c.key0, c.key1, z);
-    const float sa2 = 4.0f * c.kT * d.CAf * fdd, sb2 = 4.0f * c.kT * d.CBf * fdd;
-    const float ze = z[0] * ex + z[1] * ey + z[2] * ez;
-    const float px = z[0] - ze * ex, py = z[1] - ze * ey, pz = z[2] - ze * ez;
-    const float cn = d.cT * d.inv_sqrt_dtf;
-    const float cp = cn * sqrtf(sa2) * (gi < gj ? 0.70710678118654752f : -0.70710678118654752f);
-    const float cq = cn * sqrtf(sa2 * (2.0f / 3.0f) + sb2 * (1.0f / 3.0f)) * z[3];
-    fx += cp * px + cq * ex;
-    fy += cp * py + cq * ey;
-    fz += cp * pz + cq * ez;
+    const float ze = fma(z[2], ez, fma(z[0], ex, z[1] * ey));
+    const float px = fma(-ze, ex, z[0]), py = fma(-ze, ey, z[1]), pz = fma(-ze, ez, z[2]);
+    const float sf = sqrtf_nr(fdd);
+    const float cp = sf * (gi < gj ? c.across : -c.across);
+    const float cq = sf * c.along * z[3];
+    fx = fma(cq, ex, fma(cp, px, fx));
+    fy = fma(cq, ey, fma(cp, py, fy));
+    fz = fma(cq, ez, fma(cp, pz, fz));
     // the torque takes the part across e (e x e = 0)
-    tx += cp * px;
-    ty += cp * py;
-    tz += cp * pz;
+    tx = fma(cp, px, tx);
+    ty = fma(cp, py, ty);
+    tz = fma(cp, pz, tz);
   }
   out[0] = fx;
   out[1] = fy;
   out[2] = fz;
   // torque: lever dx/2 along -e_ij (Sec. 2.6), lever applied to the sum
-  out[3] = ey * tz - ez * ty;
-  out[4] = ez * tx - ex * tz;
-  out[5] = ex * ty - ey * tx;
+  out[3] = fma(ey, tz, -(ez * ty));
+  out[4] = fma(ez, tx, -(ex * tz));
+  out[5] = fma(ex, ty, -(ey * tx));
   out[6] = cx_;
   out[7] = cy_;
   out[8] = cz_;
@@ -752,14 +754,13 @@ __device__ __forceinline__ void pair_terms(const Dev& d, const PairCtx& c, const
   out[9] = STRESS ? ((rj.type == T_FLUID || rj.type == T_INNER) ? 0.5f : 1.0f) * rz * fx : 0.0f;
 }
 
-// the sums of the pair terms round every term and every addition, in every
-// kernel alike
+// one addition, rounded
 __device__ __forceinline__ float add_rounded(float a, float b) {
 #pragma clang fp contract(off)
   return a + b;
 }
 
-template <bool NOISE, bool STRESS>
+template <bool STRESS>
 __global__ __launch_bounds__(BS) void k_fluid_forces(Dev d) {
   int i;
   const int b = blk_box<true>(d, i);
@@ -772,7 +773,7 @@ __global__ __launch_bounds__(BS) void k_fluid_forces(Dev d) {
   for (int q = 0; q < PT_N; ++q) acc[q] = 0.0f;
   if (ti == T_FLUID || ti == T_INNER) {
     const PR ri = load_pr(d.prec, i);
-    const PairCtx c = pair_ctx<NOISE>(d, B, ri);
+    const PairCtx c = pair_ctx<false>(d, B, ri);
     const int cnt = d.nbr_cnt[i];
     const int* nb = d.nbr + i;
     const size_t npad = (size_t)d.npad;
@@ -784,7 +785,7 @@ __global__ __launch_bounds__(BS) void k_fluid_forces(Dev d) {
       const PR rj = load_pr(d.prec, jn);
       jn = k + 1 < cnt ? nb[(size_t)(k + 1) * npad] : i;
       float t[PT_N];
-      pair_terms<NOISE, STRESS>(d, c, ri, rj, t);
+      pair_terms<false, STRESS>(d, c, ri, rj, t);
 #pragma unroll
       for (int q = 0; q < (STRESS ? 10 : 9); ++q) acc[q] = add_rounded(acc[q], t[q]);
     }
@@ -794,6 +795,105 @@ __global__ __launch_bounds__(BS) void k_fluid_forces(Dev d) {
   }
   const size_t np = (size_t)d.npad;
   float* o = d.fout;
+#pragma unroll
+  for (int q = 0; q < 9; ++q) o[q * np + i] = acc[q];
+  if (STRESS) o[12 * np + i] = acc[9];
+}
+
+// The thermal pair kernel of large systems.  Its arithmetic (the Philox
+// block and the normals of a pair) leaves little of the texture-address unit
+// to spare, and a lane loading its partner's 64-byte record takes that unit
+// one cycle per lane and 16 bytes: 95 % of the time.  Here the four lanes of
+// a quad load one record together, so a cycle fetches 64 bytes, straight into
+// LDS (no registers for loads in flight), and every lane then reads its own
+// partner from there; the next slot's records are on their way while a slot
+// is evaluated.  Periodic box of 4.2 M particles: 620 us per launch with
+// per-lane loads, 512 us so; 256 sheared cells' worth of spheres and fluid
+// 290 to 255 us.  (The plain pair kernel has a third of the arithmetic and
+// waits on the caches: 136 us per-lane, 143 us so on the dam break, so it
+// keeps the loads per lane.)
+//
+// A quad's record lies in LDS in the quarters' order q ^ t (t: which of its
+// lanes wants it), which spreads the lanes' reads over the banks.  WIDE_OFS:
+// byte offsets into the records need more than 32 bits.
+template <bool STRESS, bool WIDE_OFS>
+__global__ __launch_bounds__(BS) void k_fluid_forces_thermal(Dev d) {
+  __shared__ __attribute__((aligned(64))) char stage[BS * sizeof(PR)];
+  int i;
+  const int b = blk_box<true>(d, i);
+  if (b < 0) return;  // uniform over the block
+  const BoxD& B = d.boxes[b];
+  // every lane stays to load for its quad; one past the box's end as its
+  // first particle, with no slots of its own
+  const bool live = i < B.first + B.count;
+  if (!live) i = B.first;
+  const uint8_t ti = d.type[i];
+  const PR ri = load_pr(d.prec, i);
+  const PairCtx c = pair_ctx<true>(d, B, ri);
+  const int cnt = live && (ti == T_FLUID || ti == T_INNER) ? d.nbr_cnt[i] : 0;
+  const int* const nb = d.nbr + i;
+  const size_t npad = (size_t)d.npad;
+  const uint32_t lane = threadIdx.x & 63u, t = lane & 3u;
+  char* const st = stage + __builtin_amdgcn_readfirstlane((int)(threadIdx.x & ~63u)) * sizeof(PR);
+  const char* const base = reinterpret_cast<const char*>(d.prec);
+  // the records of the wave's 64 partners, 16 by 16: lane q of a quad takes
+  // quarter q ^ t of the record its lane t wants
+  auto fetch = [&](int j) {
+#define SDPDEM_FETCH(T)                                                                        \
+  {                                                                                            \
+    const uint32_t jt =                                                                        \
+        (uint32_t)__builtin_amdgcn_mov_dpp(j, (T) * 0x55, 0xF, 0xF, true);                     \
+    const uint32_t quarter = (t ^ (T)) * 16u;                                                  \
+    const char* const src = WIDE_OFS ? base + ((size_t)jt * sizeof(PR) + quarter)              \
+                                     : base + (jt * (uint32_t)sizeof(PR) + quarter);           \
+    load_to_lds16(src, st + (T) * 1024);                                                       \
+  }
+    SDPDEM_FETCH(0)
+    SDPDEM_FETCH(1)
+    SDPDEM_FETCH(2)
+    SDPDEM_FETCH(3)
+#undef SDPDEM_FETCH
+  };
+  const uint32_t mine = t * 1024u + (lane >> 2) * 64u + t * 16u;
+  int kmax = cnt;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) kmax = max(kmax, __shfl_xor(kmax, o, 64));
+  kmax = __builtin_amdgcn_readfirstlane(kmax);
+  // a lane past its row's end asks for its own record
+  int jn = cnt > 0 ? nb[0] : i;
+  int jnn = cnt > 1 ? nb[npad] : i;
+  if (kmax > 0) fetch(jn);
+  jn = jnn;
+  float acc[PT_N];
+#pragma unroll
+  for (int q = 0; q < PT_N; ++q) acc[q] = 0.0f;
+  for (int k = 0; k < kmax; ++k) {
+    wait_loads();
+    union {
+      PR r;
+      float4 q[4];
+    } rj;
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+      rj.q[m] = *reinterpret_cast<const float4*>(st + (mine ^ (uint32_t)(m * 16)));
+    wait_lds();  // read before the next records land there
+    jnn = k + 2 < cnt ? nb[(size_t)(k + 2) * npad] : i;
+    fetch(jn);
+    jn = jnn;
+    if (k < cnt) {
+      float tt[PT_N];
+      pair_terms<true, STRESS>(d, c, ri, rj.r, tt);
+#pragma unroll
+      for (int q = 0; q < (STRESS ? 10 : 9); ++q) acc[q] = add_rounded(acc[q], tt[q]);
+    }
+  }
+  wait_loads();  // no load into LDS outlives its wave
+  if (!live) return;
+  acc[3] *= -d.leverf;
+  acc[4] *= -d.leverf;
+  acc[5] *= -d.leverf;
+  const size_t np = (size_t)d.npad;
+  float* const o = d.fout;
 #pragma unroll
   for (int q = 0; q < 9; ++q) o[q * np + i] = acc[q];
   if (STRESS) o[12 * np + i] = acc[9];
@@ -865,8 +965,13 @@ static auto forces_lanes(const Dev& d, bool noise) {
 
 void launch_fluid_forces(const Dev& d, bool noise, hipStream_t st, hipEvent_t t0,
                          hipEvent_t t1) {
-  auto k = noise ? (d.stress ? k_fluid_forces<true, true> : k_fluid_forces<true, false>)
-                 : (d.stress ? k_fluid_forces<false, true> : k_fluid_forces<false, false>);
+  auto k = d.stress ? k_fluid_forces<true> : k_fluid_forces<false>;
+  if (noise) {
+    const bool ofs64 = (size_t)d.npad * sizeof(PR) > (size_t)UINT32_MAX;
+    k = d.stress ? (ofs64 ? k_fluid_forces_thermal<true, true> : k_fluid_forces_thermal<true, false>)
+                 : (ofs64 ? k_fluid_forces_thermal<false, true>
+                          : k_fluid_forces_thermal<false, false>);
+  }
   const int lanes = lanes_per_particle(d.nactive, noise ? THERMAL4_MAX : ROWS4_MAX);
   if (lanes == 16)
     k = forces_lanes<16>(d, noise);
