@@ -41,6 +41,9 @@ struct sdpdem_system {
   // the coupling action's per-sphere records hold the partners of every
   // sphere (within H_s + skin) at the current sorted order
   bool rec_valid = false;
+  // the contact partner lists match the rigid grid (with candidate reuse
+  // both stay those of the last search)
+  bool dem_valid = false;
   bool capturing = false;
   int64_t searches = 0, reuses = 0;
   // pinned host word the moved flag is copied into, and the event the host
@@ -57,7 +60,7 @@ struct sdpdem_system {
   // captured step loop (graph_steps steps, an even number, per launch)
   int graph_steps = 0;
   hipGraphExec_t gexec = nullptr;
-  bool g_act = false, g_stress = false, g_rxn = false, g_rec = false;
+  bool g_act = false, g_stress = false, g_rxn = false, g_rec = false, g_dem = false;
   // a second stream of the library's own for work that does not depend on
   // what runs beside it (the rigid grid, the sphere records, the contacts),
   // forked from the caller's stream and joined back into it within the
@@ -280,7 +283,8 @@ size_t layout(const Sizes& z, char* base, sdpdem_system* s) {
   D4* rdg_c = b.take<D4>(nr);
   int* rxn_cnt = b.take<int>(nr ? np : 1);
   int2* rxn_slot = b.take<int2>(nr ? (size_t)RXN_CAP * np : 1);
-  int* act_list = b.take<int>(nr ? (size_t)nr * ACT_ROUNDS * 64 : 1);
+  int* act_list = b.take<int>(nr ? nr * (ACT_ROUNDS * 64 + DEM_ROW) : 1);
+  int* dem_list = act_list + nr * ACT_ROUNDS * 64;
   int2* act_meta = b.take<int2>(nr ? nr : 1);
   double* act_sum = b.take<double>(nr ? 8 * (size_t)nr : 1);
   int64_t* dstep = b.take<int64_t>(1);
@@ -366,6 +370,7 @@ size_t layout(const Sizes& z, char* base, sdpdem_system* s) {
     d.rxn_slot = rxn_slot;
     d.act_list = act_list;
     d.act_meta = act_meta;
+    d.dem_list = dem_list;
     d.act_sum = act_sum;
     d.dstep = dstep;
   }
@@ -455,9 +460,6 @@ bool plan(const sdpdem_params* P, const sdpdem_box* boxes, int nbox,
     // rigid grid: cells at least H_max = R_max + h wide, so that the fluid
     // particles coupled to a sphere lie in its 27 neighbouring cells
     if (!make_grid(hb, *q, r, (rmax + P->h) * (1.0 + 1e-6), B.rg)) return false;
-    // DEM partners lie within R_s + R_k + h <= 2 R_max + h
-    double mincs = std::min(B.rg.cs[0], std::min(B.rg.cs[1], B.rg.cs[2]));
-    B.dem_reach = std::max(1, (int)std::ceil((2.0 * rmax + P->h) / mincs * (1.0 + 1e-9)));
     B.couple_R = rmax + P->h;
     // under shear every partner within H_s <= R_max + h now was within
     // H_s + skin at the search while 2 D + (R_max + h + skin) |shear| t <
@@ -466,7 +468,6 @@ bool plan(const sdpdem_params* P, const sdpdem_box* boxes, int nbox,
     B.act_margin = (hb.shear_rate != 0.0 && P->skin > 0.0)
                        ? 0.5 * hb.L[2] * P->skin / (rmax + P->h + P->skin)
                        : 0.0;
-    B.dem_R = 2.0 * rmax + P->h;
     int64_t nact = 0;
     for (int64_t k : r) nact += q->type[k] != SDPDEM_OUTER_WALL;
     B.nact = (int)nact;
@@ -704,6 +705,8 @@ bool issue_rigid(sdpdem_system* s, hipStream_t rs, bool fk, int commit) {
   const bool ok = !fk || hipEventRecord(s->ev_gather, rs) == hipSuccess;
   {
     Prof pr(s, SDPDEM_K_DEM, rs);
+    if (!s->dem_valid) launch_dem_find(d, rs);
+    s->dem_valid = true;
     launch_dem(d, commit, s->ct_cnt[nx], s->ct_partner[nx], s->ct_dt[nx], rs);
   }
   return ok;
@@ -773,12 +776,22 @@ void run_build(sdpdem_system* s, hipStream_t st, int commit_next, int lists = LI
   }
   const bool fk = fk0 && hipStreamWaitEvent(s->side, s->ev_fork, 0) == hipSuccess;
   hipStream_t rs = fk ? s->side : st;
-  if (d.nr > 0) {
+  // without a search the rigid grid and the partner lists stay, too: they
+  // hold every partner within the margin the moved flag guards
+  if (d.nr > 0 && search) {
     Prof pr(s, SDPDEM_K_RIGID_GRID, rs);
     launch_bin_rigid(d, rs);
     launch_scan(d.rcount, d.rncells_all, d.rstart, d.rcursor, s->rblock_sums, rs);
     launch_scatter(d.rkey, d.nr, d.rcursor, d.ritems, rs);
     launch_cell_sort(d.rstart, d.rncells_all, d.ritems, nullptr, rs);
+    s->dem_valid = false;
+    // the lists of a search must be those at its positions, also if the
+    // spheres only become active before the next one
+    if (d.reuse && !s->capturing && !rigid_active(s)) {
+      launch_rigid_gather(d, rs);
+      launch_dem_find(d, rs);
+      s->dem_valid = true;
+    }
   }
   if (commit_next >= 0 && rigid_active(s)) {
     s->gather_ok = issue_rigid(s, rs, fk, commit_next);
@@ -1212,6 +1225,7 @@ bool capture(sdpdem_system* s, hipStream_t st) {
   const int64_t step0 = s->step, samples0 = s->stress_samples;
   const int cur0 = s->cur, ct0 = s->ct_cur;
   const bool rxn0 = s->rxn_valid, cand0 = s->cand_valid, rec0 = s->rec_valid;
+  const bool dem0 = s->dem_valid;
   const int64_t searches0 = s->searches;
   hipGraph_t g = nullptr;
   if (hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal) != hipSuccess) return false;
@@ -1225,6 +1239,7 @@ bool capture(sdpdem_system* s, hipStream_t st) {
   s->rxn_valid = rxn0;
   s->cand_valid = cand0;
   s->rec_valid = rec0;
+  s->dem_valid = dem0;
   s->searches = searches0;
   if (s->cur != cur0 || s->ct_cur != ct0) {
     if (g) (void)hipGraphDestroy(g);
@@ -1239,6 +1254,7 @@ bool capture(sdpdem_system* s, hipStream_t st) {
   s->g_act = rigid_active(s);
   s->g_rxn = rxn0;
   s->g_rec = rec0;
+  s->g_dem = dem0;
   s->g_stress = s->stress;
   s->g_cur = s->cur;
   s->g_ct = s->ct_cur;
@@ -1265,7 +1281,8 @@ int sdpdem_step(sdpdem_system* s, int64_t nsteps, void* hip_stream) {
       // eager steps since the capture swaps them) and whether its first
       // pass refills the coupling slots: capture again when either differs
       if (!s->gexec || s->g_act != act_now || s->g_stress != s->stress || s->g_cur != s->cur ||
-          s->g_ct != s->ct_cur || s->g_rxn != s->rxn_valid || s->g_rec != s->rec_valid) {
+          s->g_ct != s->ct_cur || s->g_rxn != s->rxn_valid || s->g_rec != s->rec_valid ||
+          s->g_dem != s->dem_valid) {
         if (!capture(s, st)) {
           s->graph_steps = 0;  // capture unavailable: stay eager
           continue;
@@ -1275,6 +1292,7 @@ int sdpdem_step(sdpdem_system* s, int64_t nsteps, void* hip_stream) {
       s->rxn_valid = act_now;  // the last pass built and (with the coupling) refilled
       s->cand_valid = false;  // every replayed step searched, without candidates
       s->rec_valid = act_now;  // and (with the coupling) filled by a search
+      s->dem_valid = act_now;
       s->searches += K;
       s->step += K;
       s->graph_steps_run += K;

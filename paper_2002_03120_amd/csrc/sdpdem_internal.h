@@ -16,7 +16,10 @@ static constexpr int BS = 256;  // threads per block of the particle kernels
 static constexpr int RXN_CAP = 16;
 // candidate rounds (64 lanes each) of a sphere's coupling search that the
 // action records for the next pass; a longer search is repeated instead
-static constexpr int ACT_ROUNDS = 16;
+static constexpr int ACT_ROUNDS = 15;
+// lanes per sphere in the contact kernels, and ints per sphere of its partner
+// list (the count and up to DEM_ROW - 1 partners)
+static constexpr int DEM_G = 16, DEM_ROW = 64;
 
 enum : uint8_t { T_FLUID = 0, T_RIGID = 1, T_INNER = 2, T_OUTER = 3 };
 
@@ -81,13 +84,11 @@ struct BoxD {
   int nact;           // its first nact particles move or feel forces; the rest are outer walls
   int wall_off;       // outer walls bin into cells cell_off + wall_off + c (0: the box has none)
   int blk_first;      // the box's first entry in the launch-block table
-  int dem_reach;      // rigid-grid cells to search for DEM partners
   double couple_R;    // R_max + h: coupling partners lie within it
   // candidate reuse under shear: the flow brings two particles at most
   // shear_reach t closer (|shear| (R_max + h + skin)); the coupling search
   // reaches act_margin farther, the flow's largest drift before a search
   double shear_reach, act_margin;
-  double dem_R;       // 2 R_max + h: DEM and lubrication partners lie within it
   int noise;          // thermal forces on
   float kTf;
   uint32_t key0, key1;
@@ -207,6 +208,7 @@ struct Dev {
   // round of its search (-1: none), and (rounds or -1, rigid centres in H_s)
   int* act_list;  // [nr][ACT_ROUNDS * 64]
   int2* act_meta;
+  int* dem_list;  // [nr][DEM_ROW] by cell-ordered record: count (-1: too many), partner records
   // per cell-ordered sphere record: the action's sums Omega_s, sum w v (3),
   // sum w (F^C + F^D) (3) and the lever sum w r_z, for the finishing kernel
   double* act_sum;  // [nr][8]
@@ -265,6 +267,8 @@ void launch_rigid_gather(const Dev& d, hipStream_t st);
 // last sort (every particle within skin/2 of where that sort saw it)
 void launch_fpi_action(const Dev& d, bool fill, bool use_rec, hipStream_t st);
 void launch_fpi_reaction(const Dev& d, hipStream_t st);
+// the partner lists of the rigid grid's spheres at the gathered records
+void launch_dem_find(const Dev& d, hipStream_t st);
 void launch_dem(const Dev& d, int commit, int* nxt_cnt, int* nxt_partner, double* nxt_dt,
                 hipStream_t st);
 // with end_step, block 0 also advances the device step counter; with

@@ -697,7 +697,10 @@ __device__ __forceinline__ void reaction_of(const Dev& d, const BoxD& B, int i, 
     int oob = 0;
     int cc[3] = {cell_coord(pi.x, gr, 0, &oob), cell_coord(pi.y, gr, 1, &oob),
                  cell_coord(pi.z, gr, 2, &oob)};
-    for_stencil<false>(G, gr, coff, pi.x, pi.y, pi.z, B.couple_R, cc, 1, [&](int cb, int ce) {
+    // with candidate reuse the grid holds the spheres where the last search
+    // saw them
+    const double R = B.couple_R + d.pad + B.act_margin;
+    for_stencil<false>(G, gr, coff, pi.x, pi.y, pi.z, R, cc, reach_cells(gr, R), [&](int cb, int ce) {
       int tb = d.rstart[cb], te = d.rstart[ce];
       for (int t = tb; t < te; ++t) {
         D4 g = d.rdg_c[t];
@@ -745,8 +748,8 @@ void launch_fpi_reaction(const Dev& d, hipStream_t st) {
 
 // ---------------------------------------------------------------------------
 // (a8) DEM contacts (Sec. 2.2) and lubrication (Sec. 2.3), FP64, over the
-// cell-ordered rigid records: one wavefront per rigid particle, one
-// candidate partner per lane.  The contact table row of a particle holds
+// cell-ordered rigid records, one candidate partner per lane.  The contact
+// table row of a particle holds
 // partner ids and tangential displacements; commit (second pass) writes the
 // next table: the updated history of every pair still in contact, in
 // candidate order (ballot + prefix count, so the order is deterministic).
@@ -855,39 +858,37 @@ __device__ __forceinline__ int dem_pair_eval(const Dev& d, const Geo& G, int s, 
   return 0;
 }
 
-// at most 128 registers (four waves per SIMD instead of three; a few
-// spills, 7 % faster over the dam break's 20,000 spheres)
-__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_dem(
-    Dev d, int commit, int* nxt_cnt, int* nxt_partner, double* nxt_dt) {
-  const int wave = xcd_wave();
-  const int lane = threadIdx.x & 63;
-  if (wave >= d.nr) return;
-  // spheres in rigid-grid cell order: neighbouring waves share cache lines
-  const int me = wave;
-  const int s = __builtin_amdgcn_readfirstlane(d.ritems[me]);
-  const BoxD& B = d.boxes[__builtin_amdgcn_readfirstlane(d.rbox[s])];
-  const Geo G = geo_of(B);
+// Two kernels: the search lists every sphere's partners, the evaluation runs
+// over the lists.  The lists hold the partners within R_s + R_k + h plus the
+// margin that candidate reuse needs, so every pass until the next search of
+// the fluid grid reads them: no second search in the other pass of a step,
+// and with reuse no rigid grid to rebuild at all in most steps.  Both take
+// DEM_G lanes per sphere, four spheres to a wave (a sphere has 5 to 25
+// partners).  Bound by latency, and by the share of the chip the kernels beside
+// it leave.  Dam break, 20,000 spheres, beside the fluid kernels: 66 us per
+// pass (18 alone) against 170 to 209 (60) of a wave per sphere that searched
+// in every pass; the search itself, 114 us, runs with the fluid's.
+
+// Calls fn(record, valid) for the spheres of the cells within R of sphere ps
+// in the rigid grid of box B, one per lane of the group and round, in cell
+// order; every lane of the group makes the same calls.
+template <class Fn>
+__device__ __forceinline__ void for_rigid_near(const Dev& d, const BoxD& B, const Geo& G,
+                                               const D4& ps, double R, Fn&& fn) {
   const Grid gr = B.rg;
-  const int coff = B.rcell_off, reach = B.dem_reach;
-  // partners k lie within R_s + R_k + h <= R_s + (R_max + h)
-  const double dem_Rk = B.couple_R;
-  const D4 ps = d.rpos_c[me], vs = d.rvel_c[me], ws = d.rom_c[me];
+  const int coff = B.rcell_off;
+  const int g = (int)threadIdx.x % DEM_G;
   int oob = 0;
-  int cc[3] = {cell_coord(ps.x, gr, 0, &oob), cell_coord(ps.y, gr, 1, &oob),
-               cell_coord(ps.z, gr, 2, &oob)};
-  const int mc = d.maxc;
-  const int ocnt = d.ct_cnt[s];
-  DemAcc acc = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}, 0.0};
-  int ncnt = 0;
-  int overflow = 0;
-  const StencilShape sh = stencil_shape(gr, cc, reach);
+  const int cc[3] = {cell_coord(ps.x, gr, 0, &oob), cell_coord(ps.y, gr, 1, &oob),
+                     cell_coord(ps.z, gr, 2, &oob)};
+  const int kr = reach_cells(gr, R);
+  const StencilShape sh = stencil_shape(gr, cc, kr);
   const int nrows = sh.zn * sh.yn;
-  for (int rb = 0; rb < nrows; rb += 64) {
+  for (int rb = 0; rb < nrows; rb += DEM_G) {
     int sa = 0, la = 0, sb = 0, lb = 0;
-    if (rb + lane < nrows) {
+    if (rb + g < nrows) {
       int a0, a1, b0, b1;
-      stencil_row<true>(G, gr, coff, ps.x, ps.y, ps.z, ps.w + dem_Rk, cc, reach, sh, rb + lane,
-                        a0, a1, b0, b1);
+      stencil_row<true>(G, gr, coff, ps.x, ps.y, ps.z, R, cc, kr, sh, rb + g, a0, a1, b0, b1);
       if (a1 > a0) {
         sa = d.rstart[a0];
         la = d.rstart[a1] - sa;
@@ -897,78 +898,150 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_
         lb = d.rstart[b1] - sb;
       }
     }
-    const int len = la + lb;
-    int inc = len;
+    int inc = la + lb;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      int t = __shfl_up(inc, o, 64);
-      if (lane >= o) inc += t;
+    for (int o = 1; o < DEM_G; o <<= 1) {
+      const int t = __shfl_up(inc, o, DEM_G);
+      if (g >= o) inc += t;
     }
-    const int total = __shfl(inc, 63, 64);
-    const int off = inc - len;
-    for (int base = 0; base < total; base += 64) {
-      const int t = base + lane;
+    const int total = __shfl(inc, DEM_G - 1, DEM_G);
+    const int off = inc - la - lb;
+    for (int t = g; t - g < total; t += DEM_G) {
       int r = 0;  // last row whose offset is <= t
 #pragma unroll
-      for (int stp = 32; stp > 0; stp >>= 1) {
-        int cand = r + stp;
-        int v = __shfl(off, cand & 63, 64);
-        if (cand < 64 && v <= t) r = cand;
-      }
-      const int offr = __shfl(off, r, 64);
-      const int sar = __shfl(sa, r, 64);
-      const int lar = __shfl(la, r, 64);
-      const int sbr = __shfl(sb, r, 64);
-      int contact = 0, gk = -1;
-      double nd[3] = {0, 0, 0};
-      if (t < total) {
-        const int q = t - offr;
-        const int tt = q < lar ? sar + q : sbr + (q - lar);
-        if (tt != me) contact = dem_pair_eval(d, G, s, ps, vs, ws, tt, ocnt, acc, gk, nd);
-      }
-      if (commit) {
-        // contacts of this round in candidate order
-        const uint64_t m = __ballot(contact);
-        const int before = __popcll(m & ((1ull << lane) - 1ull));
-        const int slot = ncnt + before;
-        if (contact) {
-          if (slot < mc) {
-            nxt_partner[s * mc + slot] = gk;
-            nxt_dt[(size_t)(s * mc + slot) * 3 + 0] = nd[0];
-            nxt_dt[(size_t)(s * mc + slot) * 3 + 1] = nd[1];
-            nxt_dt[(size_t)(s * mc + slot) * 3 + 2] = nd[2];
-          } else {
-            overflow = 1;
-          }
-        }
-        ncnt += __popcll(m);
-      }
+      for (int stp = DEM_G / 2; stp > 0; stp >>= 1)
+        if (__shfl(off, r + stp, DEM_G) <= t) r += stp;
+      const int q = t - __shfl(off, r, DEM_G);
+      const int lar = __shfl(la, r, DEM_G);
+      const int sar = __shfl(sa, r, DEM_G), sbr = __shfl(sb, r, DEM_G);
+      fn(q < lar ? sar + q : sbr + (q - lar), t < total);
     }
   }
-  for (int a = 0; a < 3; ++a) {
-    acc.F[a] = wave_sum(acc.F[a]);
-    acc.FL[a] = wave_sum(acc.FL[a]);
-    acc.N[a] = wave_sum(acc.N[a]);
+}
+
+// the lanes of this group for which p holds, as bits 0 .. DEM_G - 1
+__device__ __forceinline__ unsigned dem_ballot(bool p) {
+  const int base = (int)(threadIdx.x & 63) & ~(DEM_G - 1);
+  return (unsigned)(__ballot(p) >> base) & ((1u << DEM_G) - 1u);
+}
+
+// Runs body(box) for the wave's groups box by box, the box uniform (its
+// constants are scalar loads then): nearly always one turn, since a box's
+// spheres follow each other.
+template <class Fn>
+__device__ __forceinline__ void by_box(const Dev& d, int box, Fn&& body) {
+  bool todo = box >= 0;
+  while (todo) {
+    const int b = __builtin_amdgcn_readfirstlane(box);
+    if (box == b) {
+      body(d.boxes[b]);
+      todo = false;
+    }
   }
-  if (d.stress) acc.Wzx = wave_sum(acc.Wzx);
-  overflow = __any(overflow);
-  if (lane != 0) return;
-  for (int a = 0; a < 3; ++a) {
-    d.f_dem[3 * s + a] = acc.F[a];
-    d.f_lub[3 * s + a] = acc.FL[a];
-    d.n_dem[3 * s + a] = acc.N[a];
-  }
-  if (d.stress) d.wzx_r[2 * s + 1] = acc.Wzx;
-  if (commit) {
-    nxt_cnt[s] = ncnt < mc ? ncnt : mc;
-    if (overflow || ncnt > mc) atomicOr(d.status, ST_CONTACT_OVERFLOW);
-  }
+}
+
+__global__ __launch_bounds__(BS) void k_dem_find(Dev d) {
+  const int me = (xcd_wave() * 64 + (int)(threadIdx.x & 63)) / DEM_G;
+  const int g = (int)threadIdx.x % DEM_G;
+  const int box = me < d.nr ? d.rbox[d.ritems[me]] : -1;
+  by_box(d, box, [&](const BoxD& B) {
+    const Geo G = geo_of(B);
+    const D4 ps = d.rpos_c[me];
+    // partners come within R_s + R_k + h before the next search if they are
+    // within 2 skin more of it now (pad: skin / 2)
+    const double reach = ps.w + d.h + 4.0 * d.pad * (1.0 + 1e-9);
+    int* const list = d.dem_list + (size_t)me * DEM_ROW;
+    int cnt = 0;
+    for_rigid_near(d, B, G, ps, reach + (B.couple_R - d.h), [&](int t, bool valid) {
+      bool in = false;
+      if (valid && t != me) {
+        const D4 pk = d.rpos_c[t];
+        double e0 = ps.x - pk.x, e1 = ps.y - pk.y, e2 = ps.z - pk.z;
+        min_img_box(G, e0, e1, e2);
+        const double lim = reach + pk.w;
+        in = r2_exact(e0, e1, e2) < lim * lim;
+      }
+      const unsigned m = dem_ballot(in);
+      const int slot = cnt + __popc(m & ((1u << g) - 1u));
+      if (in && slot < DEM_ROW - 1) list[1 + slot] = t;
+      cnt += __popc(m);
+    });
+    if (g == 0) list[0] = cnt < DEM_ROW ? cnt : -1;  // -1: more than the row holds
+  });
+}
+
+// at most 128 registers: four waves per SIMD
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_dem(
+    Dev d, int commit, int* nxt_cnt, int* nxt_partner, double* nxt_dt) {
+  const int me = (xcd_wave() * 64 + (int)(threadIdx.x & 63)) / DEM_G;
+  const int g = (int)threadIdx.x % DEM_G;
+  const int s = me < d.nr ? d.ritems[me] : -1;
+  const int box = s >= 0 ? d.rbox[s] : -1;
+  by_box(d, box, [&](const BoxD& B) {
+    const Geo G = geo_of(B);
+    const D4 ps = d.rpos_c[me], vs = d.rvel_c[me], ws = d.rom_c[me];
+    const int mc = d.maxc;
+    const int ocnt = d.ct_cnt[s];
+    DemAcc acc = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}, 0.0};
+    int ncnt = 0;
+    // one partner per lane and round; commits keep the contacts in list order
+    auto round = [&](int t, bool valid) {
+      int contact = 0, gk = -1;
+      double nd[3] = {0, 0, 0};
+      if (valid && t != me) contact = dem_pair_eval(d, G, s, ps, vs, ws, t, ocnt, acc, gk, nd);
+      if (commit) {
+        const unsigned m = dem_ballot(contact);
+        const int slot = ncnt + __popc(m & ((1u << g) - 1u));
+        if (contact && slot < mc) {
+          nxt_partner[s * mc + slot] = gk;
+          nxt_dt[(size_t)(s * mc + slot) * 3 + 0] = nd[0];
+          nxt_dt[(size_t)(s * mc + slot) * 3 + 1] = nd[1];
+          nxt_dt[(size_t)(s * mc + slot) * 3 + 2] = nd[2];
+        }
+        ncnt += __popc(m);
+      }
+    };
+    const int* const list = d.dem_list + (size_t)me * DEM_ROW;
+    const int cnt = list[0];
+    if (cnt >= 0) {
+      for (int k = g; k - g < cnt; k += DEM_G) round(k < cnt ? list[1 + k] : me, k < cnt);
+    } else {
+      // more partners than the row holds: search (the grid may hold a sphere
+      // where the last search of the fluid grid saw it)
+      for_rigid_near(d, B, G, ps, ps.w + B.couple_R + d.pad + B.act_margin, round);
+    }
+#pragma unroll
+    for (int o = DEM_G / 2; o > 0; o >>= 1) {
+      for (int a = 0; a < 3; ++a) {
+        acc.F[a] += __shfl_xor(acc.F[a], o, DEM_G);
+        acc.FL[a] += __shfl_xor(acc.FL[a], o, DEM_G);
+        acc.N[a] += __shfl_xor(acc.N[a], o, DEM_G);
+      }
+      if (d.stress) acc.Wzx += __shfl_xor(acc.Wzx, o, DEM_G);
+    }
+    if (g != 0) return;
+    for (int a = 0; a < 3; ++a) {
+      d.f_dem[3 * s + a] = acc.F[a];
+      d.f_lub[3 * s + a] = acc.FL[a];
+      d.n_dem[3 * s + a] = acc.N[a];
+    }
+    if (d.stress) d.wzx_r[2 * s + 1] = acc.Wzx;
+    if (commit) {
+      nxt_cnt[s] = ncnt < mc ? ncnt : mc;
+      if (ncnt > mc) atomicOr(d.status, ST_CONTACT_OVERFLOW);
+    }
+  });
+}
+
+void launch_dem_find(const Dev& d, hipStream_t st) {
+  if (d.nr == 0) return;
+  k_dem_find<<<nblocks((size_t)d.nr * DEM_G), BS, 0, st>>>(d);
 }
 
 void launch_dem(const Dev& d, int commit, int* nxt_cnt, int* nxt_partner, double* nxt_dt,
                 hipStream_t st) {
   if (d.nr == 0) return;
-  k_dem<<<nblocks((size_t)d.nr * 64), BS, 0, st>>>(d, commit, nxt_cnt, nxt_partner, nxt_dt);
+  k_dem<<<nblocks((size_t)d.nr * DEM_G), BS, 0, st>>>(d, commit, nxt_cnt, nxt_partner, nxt_dt);
 }
 
 // ---------------------------------------------------------------------------
