@@ -55,6 +55,7 @@ struct sdpdem_system {
   // and sorted order (a neighbour build invalidates them)
   bool rxn_valid = false;
   bool noise = false;
+  bool dense = false;  // a fluid particle couples to kDenseCoupling spheres or more on average
   bool stress = false;
   int64_t stress_samples = 0;
   // captured step loop (graph_steps steps, an even number, per launch)
@@ -89,6 +90,13 @@ struct sdpdem_system {
 namespace {
 
 constexpr double kPi = 3.14159265358979323846;
+// Coupled spheres per fluid particle from which the reaction takes a launch
+// of its own with several lanes per particle: near RXN_CAP many particles
+// overflow their slots and search alone inside the update.  Slurry channel,
+// ms per 20 steps in the update / on its own: 9.74 / 7.58 at 13.7 coupled
+// spheres, 6.29 / 6.61 at 6.9, 5.99 / 6.33 at 4.6 (dam break, 2.2: 4.69 / 5.76
+// per 5 steps).
+constexpr double kDenseCoupling = 10.0;
 
 struct Bump {
   char* base;
@@ -849,10 +857,11 @@ void run_pass(sdpdem_system* s, int velver, int commit, bool integrate, bool fil
         s->rec_valid = true;  // a search-based fill records every sphere
       }
     }
-    // the reaction of an updating pass is formed inside the update
-    if (!integrate) {
+    // the reaction of an updating pass is formed inside the update, unless
+    // the fluid particles couple to many spheres each
+    if (!integrate || s->dense) {
       Prof pr(s, SDPDEM_K_FPI_REACTION, st);
-      launch_fpi_reaction(d, st);
+      launch_fpi_reaction(d, s->dense, st);
     }
   }
   if (fk) join_side(s, st);
@@ -870,7 +879,8 @@ void run_pass(sdpdem_system* s, int velver, int commit, bool integrate, bool fil
     Prof pr(s, SDPDEM_K_INTEGRATE, st);
     // the second pass of a step also advances the device step counter
     // a captured graph never reads the moved flag: no need to raise it
-    launch_integrate(d, velver, act ? 1 : 0, velver == 2, act, d.reuse && !s->capturing, st);
+    launch_integrate(d, velver, act ? 1 : 0, velver == 2, act && !s->dense,
+                     d.reuse && !s->capturing, st);
   }
 }
 
@@ -944,6 +954,16 @@ int create_impl(const sdpdem_params* params, const sdpdem_box* boxes, int nbox,
   s->cur = 0;
   s->ct_cur = 0;
   s->h_gid2slot = slot_of;
+  {
+    // coupled spheres per fluid particle: the fluid particles in every H_s
+    double vol = 0.0, nfl = 0.0;
+    for (int64_t k = 0; k < q->n; ++k) {
+      const double H = q->radius[k] + params->h;
+      if (q->type[k] == SDPDEM_RIGID) vol += 4.0 / 3.0 * kPi * H * H * H;
+      if (q->type[k] == SDPDEM_FLUID) nfl += 1.0;
+    }
+    s->dense = vol * params->rho0 / params->mass_fluid > kDenseCoupling * nfl;
+  }
   bind_current(s);
   hipStream_t st = (hipStream_t)hip_stream;
   // stage the particles box by box, ids ascending inside a box: the order

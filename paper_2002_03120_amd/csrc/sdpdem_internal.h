@@ -266,7 +266,8 @@ void launch_rigid_gather(const Dev& d, hipStream_t st);
 // sphere's partners; use_rec: the partners come from the records of the
 // last sort (every particle within skin/2 of where that sort saw it)
 void launch_fpi_action(const Dev& d, bool fill, bool use_rec, hipStream_t st);
-void launch_fpi_reaction(const Dev& d, hipStream_t st);
+// wide: several lanes per particle, for dense suspensions
+void launch_fpi_reaction(const Dev& d, bool wide, hipStream_t st);
 // the partner lists of the rigid grid's spheres at the gathered records
 void launch_dem_find(const Dev& d, hipStream_t st);
 void launch_dem(const Dev& d, int commit, int* nxt_cnt, int* nxt_partner, double* nxt_dt,

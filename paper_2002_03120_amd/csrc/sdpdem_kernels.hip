@@ -651,9 +651,94 @@ void launch_fpi_action(const Dev& d, bool fill, bool use_rec, hipStream_t st) {
   f<<<(d.nr + 63) / 64, 64, 0, st>>>(d);
 }
 
+// Calls fn(record, valid) for the spheres of the cells within R of point ps
+// in the rigid grid of box B, one per lane of the group and round, in cell
+// order; every lane of the group makes the same calls.
+template <class Fn>
+__device__ __forceinline__ void for_rigid_near(const Dev& d, const BoxD& B, const Geo& G,
+                                               const D4& ps, double R, Fn&& fn) {
+  const Grid gr = B.rg;
+  const int coff = B.rcell_off;
+  const int g = (int)threadIdx.x % DEM_G;
+  int oob = 0;
+  const int cc[3] = {cell_coord(ps.x, gr, 0, &oob), cell_coord(ps.y, gr, 1, &oob),
+                     cell_coord(ps.z, gr, 2, &oob)};
+  const int kr = reach_cells(gr, R);
+  const StencilShape sh = stencil_shape(gr, cc, kr);
+  const int nrows = sh.zn * sh.yn;
+  for (int rb = 0; rb < nrows; rb += DEM_G) {
+    int sa = 0, la = 0, sb = 0, lb = 0;
+    if (rb + g < nrows) {
+      int a0, a1, b0, b1;
+      stencil_row<true>(G, gr, coff, ps.x, ps.y, ps.z, R, cc, kr, sh, rb + g, a0, a1, b0, b1);
+      if (a1 > a0) {
+        sa = d.rstart[a0];
+        la = d.rstart[a1] - sa;
+      }
+      if (b1 > b0) {
+        sb = d.rstart[b0];
+        lb = d.rstart[b1] - sb;
+      }
+    }
+    int inc = la + lb;
+#pragma unroll
+    for (int o = 1; o < DEM_G; o <<= 1) {
+      const int t = __shfl_up(inc, o, DEM_G);
+      if (g >= o) inc += t;
+    }
+    const int total = __shfl(inc, DEM_G - 1, DEM_G);
+    const int off = inc - la - lb;
+    for (int t = g; t - g < total; t += DEM_G) {
+      int r = 0;  // last row whose offset is <= t
+#pragma unroll
+      for (int stp = DEM_G / 2; stp > 0; stp >>= 1)
+        if (__shfl(off, r + stp, DEM_G) <= t) r += stp;
+      const int q = t - __shfl(off, r, DEM_G);
+      const int lar = __shfl(la, r, DEM_G);
+      const int sar = __shfl(sa, r, DEM_G), sbr = __shfl(sb, r, DEM_G);
+      fn(q < lar ? sar + q : sbr + (q - lar), t < total);
+    }
+  }
+}
+
+// the lanes of this group for which p holds, as bits 0 .. DEM_G - 1
+__device__ __forceinline__ unsigned dem_ballot(bool p) {
+  const int base = (int)(threadIdx.x & 63) & ~(DEM_G - 1);
+  return (unsigned)(__ballot(p) >> base) & ((1u << DEM_G) - 1u);
+}
+
+// Runs body(box) for the wave's groups box by box, the box uniform (its
+// constants are scalar loads then): nearly always one turn, since a box's
+// spheres follow each other.
+template <class Fn>
+__device__ __forceinline__ void by_box(const Dev& d, int box, Fn&& body) {
+  bool todo = box >= 0;
+  while (todo) {
+    const int b = __builtin_amdgcn_readfirstlane(box);
+    if (box == b) {
+      body(d.boxes[b]);
+      todo = false;
+    }
+  }
+}
+
 // (a7) reaction on the coupled fluid particles, Eq. F_fpi_DG_reac
 // normalised per rigid particle: -sum_s F^DG_s w_sj / Omega_s over the
 // rigid s with j in C_s.  The rigid grid's cells are at least H_max wide.
+// Lucy weight of support H_s without its normalisation (folded into the
+// sphere's record; inv_H is 0 where the sphere couples to nothing): 0 outside
+__device__ __forceinline__ double reaction_weight(const Dev& d, const Geo& G, const D4& pi,
+                                                  const D4& ps, double inv_H) {
+#pragma clang fp contract(off)
+  const double H = ps.w + d.h;
+  double ex = ps.x - pi.x, ey = ps.y - pi.y, ez = ps.z - pi.z;
+  min_img_box(G, ex, ey, ez);
+  const double r2 = r2_exact(ex, ey, ez);
+  if (inv_H == 0.0 || !(r2 < H * H)) return 0.0;
+  const double q = sqrt(r2) * inv_H, omq = 1.0 - q;
+  return (1.0 + 3.0 * q) * omq * omq * omq;
+}
+
 // The reaction on fluid particle i with c > 0 coupling slots; also stored
 // in the F_RXN planes (read by the field readout and, when not fused, by
 // the update).  Returns the stored FP32 values.
@@ -684,9 +769,9 @@ __device__ __forceinline__ void reaction_of(const Dev& d, const BoxD& B, int i, 
         }
       last = best;
       const D4 g = d.rdg_c[best];
-      a0 -= g.x * (double)bw;
-      a1 -= g.y * (double)bw;
-      a2 -= g.z * (double)bw;
+      a0 = __builtin_fma(-g.x, (double)bw, a0);
+      a1 = __builtin_fma(-g.y, (double)bw, a1);
+      a2 = __builtin_fma(-g.z, (double)bw, a2);
     }
   } else {
     // more spheres than slots: search the rigid grid
@@ -703,20 +788,11 @@ __device__ __forceinline__ void reaction_of(const Dev& d, const BoxD& B, int i, 
     for_stencil<false>(G, gr, coff, pi.x, pi.y, pi.z, R, cc, reach_cells(gr, R), [&](int cb, int ce) {
       int tb = d.rstart[cb], te = d.rstart[ce];
       for (int t = tb; t < te; ++t) {
-        D4 g = d.rdg_c[t];
-        if (g.w == 0.0) continue;
-        D4 ps = d.rpos_c[t];
-        double H = ps.w + d.h;
-        double ex = ps.x - pi.x, ey = ps.y - pi.y, ez = ps.z - pi.z;
-        min_img_box(G, ex, ey, ez);
-        double r2 = r2_exact(ex, ey, ez);
-        if (!(r2 < H * H)) continue;
-        // Lucy weight of support H without its normalisation (folded into g)
-        const double q = sqrt(r2) * g.w, omq = 1.0 - q;
-        const double w = (1.0 + 3.0 * q) * omq * omq * omq;
-        a0 -= g.x * w;
-        a1 -= g.y * w;
-        a2 -= g.z * w;
+        const D4 g = d.rdg_c[t];
+        const double w = reaction_weight(d, G, pi, d.rpos_c[t], g.w);
+        a0 = __builtin_fma(-g.x, w, a0);
+        a1 = __builtin_fma(-g.y, w, a1);
+        a2 = __builtin_fma(-g.z, w, a2);
       }
     });
   }
@@ -742,8 +818,66 @@ __global__ __launch_bounds__(BS) void k_fpi_reaction(Dev d) {
   reaction_of(d, B, i, c, out);
 }
 
-void launch_fpi_reaction(const Dev& d, hipStream_t st) {
-  k_fpi_reaction<<<d.nablk, BS, 0, st>>>(d);
+// The same with DEM_G lanes per particle, for suspensions whose fluid
+// particles couple to many spheres: a lane per slot (or candidate sphere of
+// the search), the terms passed through LDS and added in the one-lane order,
+// the same bits.  Bound by latency; the one-lane form gathers a particle's
+// sphere records one after the other and, past RXN_CAP slots, walks the
+// rigid grid alone: slurry channel of 75,000 particles with 13.7 coupled
+// spheres each, 109 us inside the update, 29 here and 10 for the update.
+__global__ __launch_bounds__(BS) void k_fpi_reaction_wide(Dev d) {
+  __shared__ D4 terms[BS];  // -F^DG share (3) and weight
+  int i0;
+  const int b = blk_box_split<DEM_G, true>(d, i0);
+  if (b < 0) return;  // uniform over the block
+  const BoxD& B = d.boxes[b];
+  const int i = i0 + (int)threadIdx.x / DEM_G, g = (int)threadIdx.x % DEM_G;
+  if (i >= B.first + B.count) return;
+  const int c = d.rxn_cnt[i];
+  if (c == 0) return;
+  const size_t np = (size_t)d.npad;
+  D4* const grp = terms + ((int)threadIdx.x & ~(DEM_G - 1));
+  // component g of the sum, in lanes 0, 1 and 2 (the others add zeros)
+  double acc = 0.0;
+  auto add = [&](int m) {
+    const double* v = reinterpret_cast<const double*>(grp);
+    for (int l = 0; l < m; ++l) acc = __builtin_fma(v[4 * l + (g & 3)], v[4 * l + 3], acc);
+  };
+  if (c <= RXN_CAP) {
+    static_assert(RXN_CAP <= DEM_G, "a lane per slot");
+    const int2 sl = g < c ? d.rxn_slot[(size_t)g * np + i] : make_int2(INT_MAX, 0);
+    int rank = 0;  // in ascending sphere-record order
+#pragma unroll
+    for (int l = 0; l < DEM_G; ++l) rank += __shfl(sl.x, l, DEM_G) < sl.x ? 1 : 0;
+    if (g < c) {
+      const D4 f = d.rdg_c[sl.x];
+      grp[rank] = D4{-f.x, -f.y, -f.z, (double)__int_as_float(sl.y)};
+    }
+    wave_lds_sync();
+    add(c);
+  } else {
+    const D4 pi = d.pos[i];
+    const Geo G = geo_of(B);
+    for_rigid_near(d, B, G, pi, B.couple_R + d.pad + B.act_margin, [&](int t, bool valid) {
+      D4 v = {0.0, 0.0, 0.0, 0.0};
+      if (valid) {
+        const D4 f = d.rdg_c[t];
+        v = D4{-f.x, -f.y, -f.z, reaction_weight(d, G, pi, d.rpos_c[t], f.w)};
+      }
+      wave_lds_sync();
+      grp[g] = v;
+      wave_lds_sync();
+      add(DEM_G);
+    });
+  }
+  if (g < 3) d.fout[(size_t)(9 + g) * np + i] = (float)acc;
+}
+
+void launch_fpi_reaction(const Dev& d, bool wide, hipStream_t st) {
+  if (wide)
+    k_fpi_reaction_wide<<<d.nablk * DEM_G, BS, 0, st>>>(d);
+  else
+    k_fpi_reaction<<<d.nablk, BS, 0, st>>>(d);
 }
 
 // ---------------------------------------------------------------------------
@@ -868,77 +1002,6 @@ __device__ __forceinline__ int dem_pair_eval(const Dev& d, const Geo& G, int s, 
 // it leave.  Dam break, 20,000 spheres, beside the fluid kernels: 66 us per
 // pass (18 alone) against 170 to 209 (60) of a wave per sphere that searched
 // in every pass; the search itself, 114 us, runs with the fluid's.
-
-// Calls fn(record, valid) for the spheres of the cells within R of sphere ps
-// in the rigid grid of box B, one per lane of the group and round, in cell
-// order; every lane of the group makes the same calls.
-template <class Fn>
-__device__ __forceinline__ void for_rigid_near(const Dev& d, const BoxD& B, const Geo& G,
-                                               const D4& ps, double R, Fn&& fn) {
-  const Grid gr = B.rg;
-  const int coff = B.rcell_off;
-  const int g = (int)threadIdx.x % DEM_G;
-  int oob = 0;
-  const int cc[3] = {cell_coord(ps.x, gr, 0, &oob), cell_coord(ps.y, gr, 1, &oob),
-                     cell_coord(ps.z, gr, 2, &oob)};
-  const int kr = reach_cells(gr, R);
-  const StencilShape sh = stencil_shape(gr, cc, kr);
-  const int nrows = sh.zn * sh.yn;
-  for (int rb = 0; rb < nrows; rb += DEM_G) {
-    int sa = 0, la = 0, sb = 0, lb = 0;
-    if (rb + g < nrows) {
-      int a0, a1, b0, b1;
-      stencil_row<true>(G, gr, coff, ps.x, ps.y, ps.z, R, cc, kr, sh, rb + g, a0, a1, b0, b1);
-      if (a1 > a0) {
-        sa = d.rstart[a0];
-        la = d.rstart[a1] - sa;
-      }
-      if (b1 > b0) {
-        sb = d.rstart[b0];
-        lb = d.rstart[b1] - sb;
-      }
-    }
-    int inc = la + lb;
-#pragma unroll
-    for (int o = 1; o < DEM_G; o <<= 1) {
-      const int t = __shfl_up(inc, o, DEM_G);
-      if (g >= o) inc += t;
-    }
-    const int total = __shfl(inc, DEM_G - 1, DEM_G);
-    const int off = inc - la - lb;
-    for (int t = g; t - g < total; t += DEM_G) {
-      int r = 0;  // last row whose offset is <= t
-#pragma unroll
-      for (int stp = DEM_G / 2; stp > 0; stp >>= 1)
-        if (__shfl(off, r + stp, DEM_G) <= t) r += stp;
-      const int q = t - __shfl(off, r, DEM_G);
-      const int lar = __shfl(la, r, DEM_G);
-      const int sar = __shfl(sa, r, DEM_G), sbr = __shfl(sb, r, DEM_G);
-      fn(q < lar ? sar + q : sbr + (q - lar), t < total);
-    }
-  }
-}
-
-// the lanes of this group for which p holds, as bits 0 .. DEM_G - 1
-__device__ __forceinline__ unsigned dem_ballot(bool p) {
-  const int base = (int)(threadIdx.x & 63) & ~(DEM_G - 1);
-  return (unsigned)(__ballot(p) >> base) & ((1u << DEM_G) - 1u);
-}
-
-// Runs body(box) for the wave's groups box by box, the box uniform (its
-// constants are scalar loads then): nearly always one turn, since a box's
-// spheres follow each other.
-template <class Fn>
-__device__ __forceinline__ void by_box(const Dev& d, int box, Fn&& body) {
-  bool todo = box >= 0;
-  while (todo) {
-    const int b = __builtin_amdgcn_readfirstlane(box);
-    if (box == b) {
-      body(d.boxes[b]);
-      todo = false;
-    }
-  }
-}
 
 __global__ __launch_bounds__(BS) void k_dem_find(Dev d) {
   const int me = (xcd_wave() * 64 + (int)(threadIdx.x & 63)) / DEM_G;
