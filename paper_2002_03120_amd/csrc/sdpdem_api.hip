@@ -747,7 +747,6 @@ void run_build(sdpdem_system* s, hipStream_t st, int commit_next, int lists = LI
       Prof pr(s, SDPDEM_K_SORT, st);
       launch_scan(d.count, nc, d.cstart, nullptr, s->block_sums, st);
       launch_scatter_ranked(d.key, d.rank, d.n, d.cstart, d.perm, st);
-      launch_cell_sort(d.cstart, nc, d.perm, s->gid[s->cur], st);
     }
     const int src = s->cur;
     s->cur ^= 1;
@@ -791,7 +790,7 @@ void run_build(sdpdem_system* s, hipStream_t st, int commit_next, int lists = LI
     launch_bin_rigid(d, rs);
     launch_scan(d.rcount, d.rncells_all, d.rstart, d.rcursor, s->rblock_sums, rs);
     launch_scatter(d.rkey, d.nr, d.rcursor, d.ritems, rs);
-    launch_cell_sort(d.rstart, d.rncells_all, d.ritems, nullptr, rs);
+    launch_cell_sort(d.rstart, d.rncells_all, d.ritems, rs);
     s->dem_valid = false;
     // the lists of a search must be those at its positions, also if the
     // spheres only become active before the next one

@@ -240,9 +240,9 @@ void launch_scatter(const uint32_t* key, int n, int* cursor, int* perm, hipStrea
 // perm[start[key[i]] + rank[i]] = i (the ranks the binning handed out)
 void launch_scatter_ranked(const uint32_t* key, const int* rank, int n, const int* start,
                            int* perm, hipStream_t st);
-// sort each cell's slice of perm by sortkey[perm[k]] (sortkey == null: by value)
-void launch_cell_sort(const int* start, int ncells, int* perm, const int* sortkey,
-                      hipStream_t st);
+// sort each cell's slice of perm
+void launch_cell_sort(const int* start, int ncells, int* perm, hipStream_t st);
+// the state in cell order, ids ascending inside a cell
 void launch_permute(const Dev& d, const D4* spos, const D4* svel, const D4* som,
                     const uint8_t* stype, const int* sgid, hipStream_t st);
 // the cell-grid search; with cand (reuse on) also the candidates within

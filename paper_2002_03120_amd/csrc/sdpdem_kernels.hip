@@ -146,6 +146,8 @@ __global__ void k_pass_prep(BoxD* boxes, int nbox, const int64_t* dstep, int add
 }
 
 void launch_pass_prep(const Dev& d, BoxD* boxes, int add, bool clear_rxn, hipStream_t st) {
+  // the offsets of boxes without shear stay zero, as created
+  if (!d.any_le && !clear_rxn) return;
   const int nfill = clear_rxn ? d.npad : 0;  // rxn_cnt is 256-byte aligned
   const int threads = max(d.nbox, (nfill + 3) / 4);
   k_pass_prep<<<(unsigned)max(1, (threads + BS - 1) / BS), BS, 0, st>>>(
@@ -209,17 +211,29 @@ __global__ __launch_bounds__(BS) void k_scan_blocksums(int* block_sums, int nb) 
     }
     carry += tot;
   }
-  if (threadIdx.x == 0) block_sums[nb] = carry;
 }
 
-// also leaves the counts at zero for the next binning (the count array is
-// read by nothing after the scan), so no fill precedes the binning
+// also leaves the counts at zero for the next binning (read by nothing after
+// the scan), so no fill precedes the binning.  PRE: where a block's offset
+// comes from: the grid is one block and has none (0), the block adds up the
+// sums of the blocks before it (1), the sums are scanned already (2).
+template <int PRE>
 __global__ __launch_bounds__(BS) void k_scan_apply(int* in, int m, const int* block_sums,
                                                   int nb, int* start, int* cursor) {
   __shared__ int lds[BS / 64 + 1];
+  __shared__ int before;
   int base = blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_ITEMS;
   int v[SCAN_ITEMS];
   load_items(in, m, base, v);
+  if (PRE == 2 && threadIdx.x == 0) before = block_sums[blockIdx.x];
+  if (PRE == 2) __syncthreads();
+  if (PRE == 1) {
+    int sum = 0, all = 0;
+    for (int k = threadIdx.x; k < (int)blockIdx.x; k += BS) sum += block_sums[k];
+    block_exclusive_scan(sum, lds, &all);
+    if (threadIdx.x == 0) before = all;
+    __syncthreads();
+  }
   if (base + SCAN_ITEMS <= m) {
     *reinterpret_cast<int4*>(in + base) = make_int4(0, 0, 0, 0);
     *reinterpret_cast<int4*>(in + base + 4) = make_int4(0, 0, 0, 0);
@@ -232,7 +246,8 @@ __global__ __launch_bounds__(BS) void k_scan_apply(int* in, int m, const int* bl
 #pragma unroll
   for (int k = 0; k < SCAN_ITEMS; ++k) s += v[k];
   int tot;
-  int ex = block_exclusive_scan(s, lds, &tot) + block_sums[blockIdx.x];
+  const int offset = PRE == 0 ? 0 : before;
+  int ex = block_exclusive_scan(s, lds, &tot) + offset;
   int e[SCAN_ITEMS];
 #pragma unroll
   for (int k = 0; k < SCAN_ITEMS; ++k) {
@@ -255,7 +270,7 @@ __global__ __launch_bounds__(BS) void k_scan_apply(int* in, int m, const int* bl
         if (cursor) cursor[base + k] = e[k];
       }
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) start[m] = block_sums[nb];
+  if ((int)blockIdx.x == nb - 1 && threadIdx.x == 0) start[m] = offset + tot;
 }
 
 int scan_block_sums_size(int m) { return (m + SCAN_TILE - 1) / SCAN_TILE + 1; }
@@ -264,9 +279,19 @@ void launch_scan(int* count, int m, int* start, int* cursor, int* block_sums,
                  hipStream_t st) {
   int nb = (m + SCAN_TILE - 1) / SCAN_TILE;
   if (nb < 1) nb = 1;
+  if (nb == 1) {
+    k_scan_apply<0><<<1, BS, 0, st>>>(count, m, block_sums, nb, start, cursor);
+    return;
+  }
   k_scan_reduce<<<nb, BS, 0, st>>>(count, m, block_sums);
+  // a launch costs 2 to 4 us; adding up to 4096 block sums from the L2 less
+  // (their number squared in all: grids beyond 8.4 M cells scan them)
+  if (nb <= 4096) {
+    k_scan_apply<1><<<nb, BS, 0, st>>>(count, m, block_sums, nb, start, cursor);
+    return;
+  }
   k_scan_blocksums<<<1, BS, 0, st>>>(block_sums, nb);
-  k_scan_apply<<<nb, BS, 0, st>>>(count, m, block_sums, nb, start, cursor);
+  k_scan_apply<2><<<nb, BS, 0, st>>>(count, m, block_sums, nb, start, cursor);
 }
 
 __global__ __launch_bounds__(BS) void k_scatter(const uint32_t* key, int n, int* cursor,
@@ -295,21 +320,18 @@ void launch_scatter_ranked(const uint32_t* key, const int* rank, int n, const in
   k_scatter_ranked<<<nblocks(n), BS, 0, st>>>(key, rank, n, start, perm);
 }
 
-// Insertion sort of each cell's slice: ties of the counting sort are
-// broken by a fixed key (the particle id), making the order deterministic.
-__global__ __launch_bounds__(BS) void k_cell_sort(const int* start, int ncells, int* perm,
-                                                 const int* sortkey) {
+// Insertion sort of each cell's slice by value, making the order of the
+// rigid counting sort deterministic.
+__global__ __launch_bounds__(BS) void k_cell_sort(const int* start, int ncells, int* perm) {
   int c = blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= ncells) return;
   int lo = start[c], hi = start[c + 1];
   for (int a = lo + 1; a < hi; ++a) {
-    int v = perm[a];
-    int kv = sortkey ? sortkey[v] : v;
+    const int v = perm[a];
     int b = a - 1;
     while (b >= lo) {
-      int w = perm[b];
-      int kw = sortkey ? sortkey[w] : w;
-      if (kw <= kv) break;
+      const int w = perm[b];
+      if (w <= v) break;
       perm[b + 1] = w;
       --b;
     }
@@ -317,23 +339,32 @@ __global__ __launch_bounds__(BS) void k_cell_sort(const int* start, int ncells, 
   }
 }
 
-void launch_cell_sort(const int* start, int ncells, int* perm, const int* sortkey,
-                      hipStream_t st) {
+void launch_cell_sort(const int* start, int ncells, int* perm, hipStream_t st) {
   if (ncells == 0) return;
-  k_cell_sort<<<(ncells + BS - 1) / BS, BS, 0, st>>>(start, ncells, perm, sortkey);
+  k_cell_sort<<<(ncells + BS - 1) / BS, BS, 0, st>>>(start, ncells, perm);
 }
 
+// Moves the state to the cell order.  The scatter left a cell's particles in
+// arrival order; a particle's place among them is the number of its cell
+// mates with a smaller id, counted here (a separate launch that sorted every
+// cell's slice took 6 to 35 us of a search, 10 us in cells of three to four
+// particles).
 __global__ __launch_bounds__(BS) void k_permute(Dev d, const D4* spos, const D4* svel,
                                                const D4* som, const uint8_t* stype,
                                                const int* sgid) {
-  int i = xcd_tid();
-  if (i >= d.n) return;
-  int o = d.perm[i];
-  d.pos[i] = spos[o];
-  d.vel[i] = svel[o];
-  d.om[i] = som[o];
-  uint8_t t = stype[o];
-  int g = sgid[o];
+  const int at = xcd_tid();
+  if (at >= d.n) return;
+  const int o = d.perm[at];
+  const uint32_t c = d.key[o];
+  const int lo = d.cstart[c], hi = d.cstart[c + 1];
+  const int g = sgid[o];
+  const D4 x = spos[o], v = svel[o], w = som[o];
+  const uint8_t t = stype[o];
+  int i = lo;
+  for (int k = lo; k < hi; ++k) i += sgid[d.perm[k]] < g ? 1 : 0;
+  d.pos[i] = x;
+  d.vel[i] = v;
+  d.om[i] = w;
   d.type[i] = t;
   d.gid[i] = g;
   if (t == T_RIGID) d.rig_sorted[d.gid2slot[g]] = i;
