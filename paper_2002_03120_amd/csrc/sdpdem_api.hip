@@ -97,6 +97,8 @@ constexpr double kPi = 3.14159265358979323846;
 // spheres, 6.29 / 6.61 at 6.9, 5.99 / 6.33 at 4.6 (dam break, 2.2: 4.69 / 5.76
 // per 5 steps).
 constexpr double kDenseCoupling = 10.0;
+constexpr int64_t kWideActionSpheres = 1024;
+constexpr double kWideActionRounds = 8.0;
 
 struct Bump {
   char* base;
@@ -955,12 +957,18 @@ int create_impl(const sdpdem_params* params, const sdpdem_box* boxes, int nbox,
   s->h_gid2slot = slot_of;
   {
     // coupled spheres per fluid particle: the fluid particles in every H_s
-    double vol = 0.0, nfl = 0.0;
+    double vol = 0.0, nfl = 0.0, most = 0.0;
     for (int64_t k = 0; k < q->n; ++k) {
-      const double H = q->radius[k] + params->h;
-      if (q->type[k] == SDPDEM_RIGID) vol += 4.0 / 3.0 * kPi * H * H * H;
+      const double H = q->radius[k] + params->h, H1 = H + params->h;
+      if (q->type[k] == SDPDEM_RIGID) {
+        vol += 4.0 / 3.0 * kPi * H * H * H;
+        most = std::max(most, 4.0 / 3.0 * kPi * H1 * H1 * H1);
+      }
       if (q->type[k] == SDPDEM_FLUID) nfl += 1.0;
     }
+    // few spheres with many search rounds (64 candidates each)
+    s->d.act_wide = z.nr <= kWideActionSpheres &&
+                    most * params->rho0 / params->mass_fluid >= kWideActionRounds * 64.0;
     s->dense = vol * params->rho0 / params->mass_fluid > kDenseCoupling * nfl;
   }
   bind_current(s);

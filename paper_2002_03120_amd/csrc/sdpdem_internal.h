@@ -139,6 +139,7 @@ struct Dev {
   const int2* ablk;  // the same over the boxes' active parts (outer walls left out)
   int nablk, ablk_per;
   int nactive;       // particles of the boxes' active parts
+  int act_wide;      // a workgroup instead of a wave per sphere in the coupling action
   const int* rbox;   // box of every rigid slot
   // particles (current buffer)
   D4* pos;  // x, y, z, radius (lever for fluid and walls)

@@ -444,11 +444,25 @@ __device__ __forceinline__ int wave_sum_i(int v) {
 // pass after a drift of less than skin/2 finds every partner within H_s.
 // With use_rec a filling pass also reads it (the candidates of a build
 // that kept the sorted order).
-template <bool STRESS, bool FILL>
-__global__ __launch_bounds__(BS) void k_fpi_action(Dev d, int use_rec) {
-  const int wave = xcd_wave();
+//
+// W > 1 gives a sphere a workgroup of W waves, wave w taking the rounds w,
+// w + W, ...; for systems of few spheres, where a wave's rounds one after the
+// other are all there is to wait for (one sphere of R = 4 dx in the
+// sedimentation box: 22 rounds).  The waves' terms of W rounds pass through
+// LDS and are added lane by lane in round order: the bits of W = 1.
+// Worth it for up to about a thousand spheres with eight or more rounds each:
+// the sedimentation box 38 us (searching) and 26 us (replaying) with a wave,
+// 19 and 15 us so; 600 spheres of three to four rounds 16 and 8, 18 and 7 us.
+template <bool STRESS, bool FILL, int W>
+__global__ __launch_bounds__(W == 1 ? BS : 64 * W) void k_fpi_action(Dev d, int use_rec) {
+  constexpr int NC = 8;  // Omega, sum w v (3), sum w F (3), sum w r_z
+  static_assert(W == 1 || W == NC, "wave c adds component c");
+  __shared__ double xch[W == 1 ? 1 : NC * W * 64];
+  __shared__ int xrig[W];
+  const int wave = W == 1 ? xcd_wave() : (int)blockIdx.x;
   const int lane = threadIdx.x & 63;
-  if (wave >= d.nr) return;
+  const int w = W == 1 ? 0 : (int)(threadIdx.x >> 6);
+  if (wave >= d.nr) return;  // uniform over the waves of a sphere
   // spheres in rigid-grid cell order: neighbouring waves share cache lines
   const int s = __builtin_amdgcn_readfirstlane(d.ritems[wave]);
   const int si = d.rig_sorted[s];
@@ -459,7 +473,10 @@ __global__ __launch_bounds__(BS) void k_fpi_action(Dev d, int use_rec) {
   const double invH = 1.0 / H, wnorm = 105.0 / (16.0 * PI * H * H * H);  // Eq. kernel
   const size_t np = (size_t)d.npad;
   int* const list = d.act_list + (size_t)s * (ACT_ROUNDS * 64);
-  double om = 0, v0 = 0, v1 = 0, v2 = 0, f0 = 0, f1 = 0, f2 = 0, l2 = 0;
+  // W = 1: the lane's sums; else lane l of wave c holds component c of lane l
+  double acc[W == 1 ? NC : 1];
+#pragma unroll
+  for (int c = 0; c < (W == 1 ? NC : 1); ++c) acc[c] = 0.0;
   int nrig = 0;
   // the pair geometry of fluid candidate j: image separation, its z image
   // and r^2 (the same operations on both paths, so the sums agree bit for bit)
@@ -470,11 +487,13 @@ __global__ __launch_bounds__(BS) void k_fpi_action(Dev d, int use_rec) {
     kz = min_img_box(G, ex, ey, ez);
     return r2_exact(ex, ey, ez);
   };
-  // one coupled fluid particle
-  auto couple = [&](int j, double r2, double ez, int kz) {
+  // the terms of one coupled fluid particle, each rounded, added to acc (W = 1)
+  // or left in t
+  auto couple = [&](int j, double r2, double ez, int kz, double* t) {
+#pragma clang fp contract(off)
     const double qh = sqrt(r2) * invH, omq = 1.0 - qh;
     const double pw = (1.0 + 3.0 * qh) * omq * omq * omq;
-    const double w = wnorm * pw;
+    const double wj = wnorm * pw;
     if (FILL) {
       // hand the pair to the reaction: one slot of j (the arrival order
       // does not matter, the reaction sums its slots by sphere record)
@@ -483,33 +502,56 @@ __global__ __launch_bounds__(BS) void k_fpi_action(Dev d, int use_rec) {
         d.rxn_slot[(size_t)slot * np + j] = make_int2(wave, __float_as_int((float)pw));
     }
     const D4 vj = d.vel[j];
-    om += w;
-    v0 += w * (vj.x + (double)kz * G.le_jump);  // image velocity (Lees-Edwards)
-    v1 += w * vj.y;
-    v2 += w * vj.z;
-    f0 += w * (double)d.fout[6 * np + j];
-    f1 += w * (double)d.fout[7 * np + j];
-    f2 += w * (double)d.fout[8 * np + j];
-    if (STRESS) l2 += w * ez;  // the coupling's lever (z part)
+    const double term[NC] = {
+        wj,
+        wj * (vj.x + (double)kz * G.le_jump),  // image velocity (Lees-Edwards)
+        wj * vj.y,
+        wj * vj.z,
+        wj * (double)d.fout[6 * np + j],
+        wj * (double)d.fout[7 * np + j],
+        wj * (double)d.fout[8 * np + j],
+        STRESS ? wj * ez : 0.0};  // the coupling's lever (z part)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      if (W == 1)
+        acc[W == 1 ? c : 0] = acc[W == 1 ? c : 0] + term[c];
+      else
+        t[W == 1 ? 0 : c] = term[c];
+    }
+  };
+  // W > 1: the end of W rounds, every lane's terms (zeros without a pair)
+  auto add = [&](const double* t) {
+#pragma clang fp contract(off)
+    if (W > 1) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) xch[(c * W + w) * 64 + lane] = t[W == 1 ? 0 : c];
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < W; ++k) acc[0] = acc[0] + xch[(w * W + k) * 64 + lane];
+      __syncthreads();
+    }
   };
   const int2 meta = FILL && !use_rec ? make_int2(-1, 0) : d.act_meta[s];
   const int stored = __builtin_amdgcn_readfirstlane(meta.x);
   int rounds = 0;  // candidate rounds of the cell search
   if (stored >= 0) {
     rounds = stored;
-    for (int r = 0; r < stored; ++r) {
-      const int e = list[r * 64 + lane];
-      if (e == -1) continue;
-      const int j = e >= 0 ? e : -2 - e;
-      double ez;
-      int kz;
-      const double r2 = geom(j, ez, kz);
-      if (r2 < H2) {
-        if (e >= 0)
-          couple(j, r2, ez, kz);
-        else
-          ++nrig;
+    for (int r = w; r - w < stored; r += W) {
+      const int e = r < stored ? list[r * 64 + lane] : -1;
+      double t[W == 1 ? 1 : NC] = {};
+      if (e != -1) {
+        const int j = e >= 0 ? e : -2 - e;
+        double ez;
+        int kz;
+        const double r2 = geom(j, ez, kz);
+        if (r2 < H2) {
+          if (e >= 0)
+            couple(j, r2, ez, kz, t);
+          else
+            ++nrig;
+        }
       }
+      add(t);
     }
   } else {
     const Grid gr = B.g;
@@ -554,7 +596,7 @@ __global__ __launch_bounds__(BS) void k_fpi_action(Dev d, int use_rec) {
       const int off = inc - len;
       // every lane takes one candidate of the concatenated runs per round;
       // all lanes stay active through the shuffles
-      for (int base = 0; base < total; base += 64, ++rounds) {
+      for (int base = 64 * w; base - 64 * w < total; base += 64 * W) {
         const int t = base + lane;
         int r = 0;  // last run whose offset is <= t
 #pragma unroll
@@ -568,6 +610,7 @@ __global__ __launch_bounds__(BS) void k_fpi_action(Dev d, int use_rec) {
         const int lar = __shfl(la, r, 64);
         const int sbr = __shfl(sb, r, 64);
         int rec = -1;  // this lane's partner of this round within H_s + skin
+        double tm[W == 1 ? 1 : NC] = {};
         if (t < total) {
           const int q = t - offr;
           const int j = q < lar ? sar + q : sbr + (q - lar);
@@ -582,24 +625,37 @@ __global__ __launch_bounds__(BS) void k_fpi_action(Dev d, int use_rec) {
               if (tj == T_RIGID)
                 ++nrig;
               else
-                couple(j, r2, ez, kz);
+                couple(j, r2, ez, kz, tm);
             }
           }
         }
-        if (FILL && rounds < ACT_ROUNDS) list[rounds * 64 + lane] = rec;
+        const int round = rounds + base / 64;
+        if (FILL && base < total && round < ACT_ROUNDS) list[round * 64 + lane] = rec;
+        add(tm);
       }
+      rounds += (total + 63) / 64;
     }
   }
-  om = wave_sum(om);
-  v0 = wave_sum(v0);
-  v1 = wave_sum(v1);
-  v2 = wave_sum(v2);
-  f0 = wave_sum(f0);
-  f1 = wave_sum(f1);
-  f2 = wave_sum(f2);
-  if (STRESS) l2 = wave_sum(l2);
   nrig = wave_sum_i(nrig);
+#pragma unroll
+  for (int c = 0; c < (W == 1 ? NC : 1); ++c)
+    if (STRESS || W > 1 || c < 7) acc[c] = wave_sum(acc[c]);
+  if (W > 1) {
+    if (lane == 0) xrig[w] = nrig;
+    __syncthreads();
+  }
   if (lane != 0) return;
+  double* const out = d.act_sum + 8 * (size_t)wave;
+  if (W > 1) {
+    out[w] = acc[0];
+    if (w != 0) return;
+    nrig = 0;
+#pragma unroll
+    for (int k = 0; k < W; ++k) nrig += xrig[k];
+  } else {
+#pragma unroll
+    for (int c = 0; c < (W == 1 ? NC : 1); ++c) out[c] = acc[c];
+  }
   // the record of this search (-1: more rounds than it holds, search
   // again) and the rigid count of this pass, for the finishing kernel
   // Only a filling search that does not read records writes one (a pass
@@ -610,15 +666,6 @@ __global__ __launch_bounds__(BS) void k_fpi_action(Dev d, int use_rec) {
     d.act_meta[s] = make_int2(stored, nrig);
   else
     d.act_meta[s] = make_int2(FILL && !use_rec && rounds <= ACT_ROUNDS ? rounds : -1, nrig);
-  double* out = d.act_sum + 8 * (size_t)wave;
-  out[0] = om;
-  out[1] = v0;
-  out[2] = v1;
-  out[3] = v2;
-  out[4] = f0;
-  out[5] = f1;
-  out[6] = f2;
-  out[7] = l2;
 }
 
 // (a6, second half) one thread per sphere, in cell order: eps, F^DG and
@@ -671,11 +718,18 @@ __global__ __launch_bounds__(BS) void k_fpi_finish(Dev d) {
   d.rdg_c[t] = rc;
 }
 
+template <int W>
+static auto action_kernel(const Dev& d, bool fill) {
+  return d.stress ? (fill ? k_fpi_action<true, true, W> : k_fpi_action<true, false, W>)
+                  : (fill ? k_fpi_action<false, true, W> : k_fpi_action<false, false, W>);
+}
+
 void launch_fpi_action(const Dev& d, bool fill, bool use_rec, hipStream_t st) {
   if (d.nr == 0) return;
-  auto k = d.stress ? (fill ? k_fpi_action<true, true> : k_fpi_action<true, false>)
-                    : (fill ? k_fpi_action<false, true> : k_fpi_action<false, false>);
-  k<<<nblocks((size_t)d.nr * 64), BS, 0, st>>>(d, use_rec ? 1 : 0);
+  if (d.act_wide)
+    action_kernel<8>(d, fill)<<<d.nr, 512, 0, st>>>(d, use_rec ? 1 : 0);
+  else
+    action_kernel<1>(d, fill)<<<nblocks((size_t)d.nr * 64), BS, 0, st>>>(d, use_rec ? 1 : 0);
   // one wavefront per block: the few thousand threads of the finish spread
   // over as many CUs as possible (its FP64 divisions and powers are latency)
   auto f = d.stress ? k_fpi_finish<true> : k_fpi_finish<false>;

@@ -64,3 +64,28 @@ def test_bits_do_not_depend_on_the_lanes_per_particle(S, kind, skin):
         assert np.array_equal(cols[:ref_cols.size], ref_cols)
         assert np.array_equal(cols[-ref_cols.size:] - (copies - 1) * n, ref_cols)
         g.close()
+
+
+@pytest.mark.parametrize("skin", [0.0, 0.2])
+def test_bits_do_not_depend_on_the_waves_per_sphere(S, skin):
+    """One large sphere per box, whose coupling takes some eighteen rounds of
+    a wave: a workgroup per sphere alone, a wave in a batch of more than 1024."""
+    cell = W.shear_cell(13, phi=0.1, d=7.0, kBT=4e-3, shear_rate=5e-2, seed=6)
+    n = cell[1]["id"].shape[0]
+    assert int((cell[1]["type"] == W.RIGID).sum()) == 1
+    p = dict(cell[0], cell_factor=0.55, skin=skin)
+    ref = None
+    for copies in (1, 1030):
+        parts, boxes, box_of = W.stack_cells([cell] * copies)
+        print(f"[case] sphere of radius 3.5 x {copies}, skin {skin}", flush=True)
+        g = S.System(p, parts, boxes=boxes, box_of=box_of)
+        g.set_stress(True)
+        assert g.step(8) == 0
+        got = {f: g.read_field(f).reshape(copies, n, -1)
+               for f in ("VEL", "F_DG", "F_PG", "F_RXN", "EPS")}
+        got["stress"] = g.box_stress()[1].reshape(copies, 1)
+        ref = ref or got
+        for f, v in got.items():
+            for b in (0, copies // 2, copies - 1):
+                assert np.array_equal(v[b], ref[f][0]), (f, b)
+        g.close()
