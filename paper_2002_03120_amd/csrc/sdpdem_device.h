@@ -466,6 +466,78 @@ __device__ __forceinline__ void wait_loads() {
 }
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
+// One row of for_stencil_pruned: z and y cells cc + dz, cc + dy of a point at
+// f (single precision, relative to its own cell), as stencil_row gives it.
+// The same margins hold: extra cells, never a missing one.
+struct PlainRows {
+  float fx, fy, fz, csx, csy, csz, icx, R2;
+  bool plain;  // the conditions for_stencil_pruned names
+};
+
+__device__ __forceinline__ PlainRows plain_rows(const Geo& B, const Grid& G, double px, double py,
+                                                double pz, double R, const int cc[3], int k) {
+  PlainRows p;
+  const double fx = px - (G.lo[0] + (double)cc[0] * G.cs[0]);
+  const double fy = py - (G.lo[1] + (double)cc[1] * G.cs[1]);
+  const double fz = pz - (G.lo[2] + (double)cc[2] * G.cs[2]);
+  p.plain = !B.le && !(G.per[2] && 2 * k + 1 > G.nc[2]) && !(G.per[1] && 2 * k + 1 > G.nc[1]) &&
+            fx > -G.cs[0] && fx < 2.0 * G.cs[0] && fy > -G.cs[1] && fy < 2.0 * G.cs[1] &&
+            fz > -G.cs[2] && fz < 2.0 * G.cs[2];
+  p.fx = (float)fx;
+  p.fy = (float)fy;
+  p.fz = (float)fz;
+  p.csx = (float)G.cs[0];
+  p.csy = (float)G.cs[1];
+  p.csz = (float)G.cs[2];
+  p.icx = (float)G.inv_cs[0];
+  p.R2 = (float)(R * R) * (1.0f + 1e-5f);
+  return p;
+}
+
+__device__ __forceinline__ void plain_row(const PlainRows& p, const Grid& G, int off,
+                                          const int cc[3], int k, int dz, int dy, int& a0, int& a1,
+                                          int& b0, int& b1) {
+  a0 = a1 = b0 = b1 = 0;
+  const int nx = G.nc[0], ny = G.nc[1], nz = G.nc[2];
+  int z = cc[2] + dz, y = cc[1] + dy;
+  if (z < 0 || z >= nz) {
+    if (!G.per[2]) return;
+    z += z < 0 ? nz : -nz;
+  }
+  if (y < 0 || y >= ny) {
+    if (!G.per[1]) return;
+    y += y < 0 ? ny : -ny;
+  }
+  const float sz = fmaxf(0.0f, fmaxf((float)dz * p.csz - p.fz, p.fz - (float)(dz + 1) * p.csz));
+  const float sy = fmaxf(0.0f, fmaxf((float)dy * p.csy - p.fy, p.fy - (float)(dy + 1) * p.csy));
+  const float d2 = sz * sz + sy * sy;
+  if (d2 >= p.R2) return;
+  const float rx = __builtin_amdgcn_sqrtf(p.R2 - d2) * (1.0f + 1e-5f) + 1e-5f * p.csx;
+  const int xa = max(cc[0] + (int)floorf((p.fx - rx) * p.icx), cc[0] - k);
+  const int xb = min(cc[0] + (int)floorf((p.fx + rx) * p.icx), cc[0] + k);
+  if (xb < xa) return;
+  const int rowkey = off + (z * ny + y) * nx;
+  if (!G.per[0]) {
+    const int lo = max(xa, 0), hi = min(xb, nx - 1);
+    if (lo <= hi) {
+      a0 = rowkey + lo;
+      a1 = rowkey + hi + 1;
+    }
+  } else if (xb - xa + 1 >= nx) {
+    a0 = rowkey;
+    a1 = rowkey + nx;
+  } else {
+    const int lo = xa < 0 ? xa + nx : (xa >= nx ? xa - nx : xa);
+    const int hi = lo + (xb - xa);  // at most one wrap
+    a0 = rowkey + lo;
+    a1 = rowkey + min(hi + 1, nx);
+    if (hi >= nx) {
+      b0 = rowkey;
+      b1 = rowkey + hi - nx + 1;
+    }
+  }
+}
+
 // Block-wide exclusive scan of one int per thread (wave64 shuffles + LDS).
 __device__ inline int block_exclusive_scan(int v, int* lds, int* total) {
   int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;

@@ -51,18 +51,22 @@ __device__ __forceinline__ double2 lucy_parts(const Dev& d, double r2) {
 // boxes, us per launch with 1 / 4 / 16 lanes (h = 1.5 dx):
 //
 //   particles               4,096           32,768         110,592         373,248
-//   search, cells of h   100/32/16       97/34/31       111/66/72      151/142/190
+//   search, cells of h   100/32/16       96/35/31       112/58/72      153/136/190
 //   candidate filter   14.5/10.6/8.5  14.7/11.1/13.9  16.7/16.0/28.6  29.5/37.4/74.9
 //   pressure filter    15.3/9.7/8.3   15.4/11.1/13.4  20.6/15.9/27.9  32.2/34.4/69.9
 //   pair forces, kT = 0 12.9/9.5/7.5  14.1/10.4/11.3  15.9/18.2/25.8  38.0/43.3/72.3
 //   pair forces, kT > 0 22.3/12.3/9.0 23.0/13.7/16.8  30.1/25.9/37.6  64.2/64.9/111
 //
-// Sixteen lanes win up to about 2^14 particles; four up to 4e5 in the
-// search, whose walk is the longest, 2.6e5 in the pressure filter, 2e5 in the
-// thermal and 1e5 in the plain pair forces and the candidate filter.
+// Sixteen lanes win up to about 2^14 particles; four up to 2.6e5 in the
+// pressure filter, 2e5 in the thermal and 1e5 in the plain pair forces and
+// the candidate filter.  In the search, whose walk is the longest, four lanes
+// win up to 6e5 particles (512,000: 178/175 us, 729,000: 230/236), 8.5e5 in
+// sheared boxes (766,801: 310/280, in cells of 0.67 h 248/243; 924,604:
+// 286/291) and 2e5 active ones between walls, whose blocks are unevenly full
+// (56^3 of water, 307,208 in all: 74/74).
 static constexpr int LANES16_MAX = 1 << 14;
-static constexpr int SEARCH4_MAX = 400000, SMOOTH4_MAX = 1 << 18, THERMAL4_MAX = 200000,
-                     ROWS4_MAX = 100000;
+static constexpr int SEARCH4_MAX = 600000, SEARCH4_SHEARED = 850000, SEARCH4_WALLED = 200000;
+static constexpr int SMOOTH4_MAX = 1 << 18, THERMAL4_MAX = 200000, ROWS4_MAX = 100000;
 static int lanes_per_particle(int particles, int max4) {
   return particles <= LANES16_MAX ? 16 : particles <= max4 ? 4 : 1;
 }
@@ -192,7 +196,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(5))) void k_
 
 // The search with G lanes per particle (bound by the chain cell starts ->
 // position -> next run of the one-lane walk: 105 us for a lattice of 8,000
-// particles in cells of h, 15 us with sixteen lanes; 187 and 65 us with four
+// particles in cells of h, 15 us with sixteen lanes; 187 and 60 us with four
 // lanes for 75,000 particles at h = 2 dx).  Lane g of a group takes every G-th
 // row of the stencil (its geometry and cell starts, which the one-lane walk
 // loads one after the other), then the lanes take the candidates of the
@@ -227,6 +231,11 @@ __device__ __forceinline__ void build_density_wide(const Dev& d, int after_drift
     const int kr = reach_cells(gr, R);
     const StencilShape sh_ = stencil_shape(gr, cc, kr);
     const int nrows = sh_.zn * sh_.yn;
+    // single-precision rows where they hold (the candidate search has no
+    // registers to spare for them: 43 -> 50 us on 83,000 particles)
+    PlainRows rows = {};
+    if (!CAND) rows = plain_rows(geo, gr, pi.x, pi.y, pi.z, R, cc, kr);
+    const float inv_yn = 1.0f / (float)sh_.yn;
     double acc = d.W0;
     int cnt = 0, ccnt = 0;
     const size_t npad = (size_t)d.npad;
@@ -240,8 +249,14 @@ __device__ __forceinline__ void build_density_wide(const Dev& d, int after_drift
       int s0 = 0, e0 = 0, s1 = 0, e1 = 0, s2 = 0, e2 = 0, s3 = 0, e3 = 0;
       if (rb + g < nrows) {
         int a0, a1, b0, b1;
-        stencil_row<true>(geo, gr, coff, pi.x, pi.y, pi.z, R, cc, kr, sh_, rb + g, a0, a1, b0,
-                          b1);
+        // row / yn without an integer division: (row + 1/2) / yn stays at
+        // least 1 / (2 yn) away from every integer
+        const int zi = (int)(((float)(rb + g) + 0.5f) * inv_yn), yi = rb + g - zi * sh_.yn;
+        if (!CAND && rows.plain)
+          plain_row(rows, gr, coff, cc, kr, zi - kr, yi - kr, a0, a1, b0, b1);
+        else
+          stencil_row_zy<true>(geo, gr, coff, pi.x, pi.y, pi.z, R, cc, kr, sh_, sh_.zlo + zi,
+                               sh_.ylo + yi, a0, a1, b0, b1);
         if (a1 > a0) {
           s0 = d.cstart[a0];
           e0 = d.cstart[a1] - s0;
@@ -270,7 +285,8 @@ __device__ __forceinline__ void build_density_wide(const Dev& d, int after_drift
       }
       const int total = __shfl(inc, G - 1, G);
       const int off = inc - e3;
-      for (int t = g; t - g < total; t += G) {
+      // candidate t of the concatenated rows (i itself past their end)
+      auto candidate = [&](int t) {
         int r = 0;  // last row whose offset is <= t
 #pragma unroll
         for (int stp = G / 2; stp > 0; stp >>= 1)
@@ -285,9 +301,13 @@ __device__ __forceinline__ void build_density_wide(const Dev& d, int after_drift
         } else {
           j = q < q0 ? f0 + q : f2 + (q - q0);
         }
+        return t < total ? j : i;
+      };
+      for (int t = g; t - g < total; t += G) {
+        const int j = candidate(t);
         bool in = false, near = false;
         double2 w = make_double2(0.0, 0.0);
-        if (t < total && j != i) {
+        if (j != i) {
           const D4 pj = d.pos[j];
           double ex = pi.x - pj.x, ey = pi.y - pj.y, ez = pi.z - pj.z;
           min_img_fast(geo, ex, ey, ez);
@@ -335,8 +355,10 @@ __device__ __forceinline__ void build_density_wide(const Dev& d, int after_drift
   }
 }
 
+// (seven waves per SIMD pay in the larger systems that take four lanes)
 template <int G>
-__global__ __launch_bounds__(BS) void k_build_density_wide(Dev d) {
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(G == 4 ? 7 : 5))) void
+k_build_density_wide(Dev d) {
   build_density_wide<G, false>(d, 0);
 }
 template <int G>
@@ -354,7 +376,9 @@ static void build_density_lanes(const Dev& d, bool cand, int after_drift, hipStr
 
 void launch_build_density(const Dev& d, bool cand, bool after_drift, hipStream_t st) {
   const int ad = after_drift ? 1 : 0;
-  const int lanes = lanes_per_particle(d.n, SEARCH4_MAX);
+  const int lanes = lanes_per_particle(d.nactive, d.any_le          ? SEARCH4_SHEARED
+                                                  : d.nactive < d.n ? SEARCH4_WALLED
+                                                                    : SEARCH4_MAX);
   if (lanes == 16)
     build_density_lanes<16>(d, cand, ad, st);
   else if (lanes == 4)

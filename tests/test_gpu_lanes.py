@@ -46,7 +46,7 @@ def test_bits_do_not_depend_on_the_lanes_per_particle(S, kind, skin):
     p, n = dict(cell[0], cell_factor=0.55, skin=skin), cell[1]["id"].shape[0]
     assert n <= 1 << 14  # 16 lanes alone
     ref = None
-    for total in (n, 60_000, 150_000, 300_000, 450_000):
+    for total in (n, 60_000, 150_000, 300_000, 450_000, 900_000):
         copies = max(1, -(-total // n))
         parts, boxes, box_of = W.stack_cells([cell] * copies)
         print(f"[case] {kind} x {copies}, n={copies * n}, skin {skin}", flush=True)
