@@ -824,6 +824,15 @@ bool needs_fill(const sdpdem_system* s, bool build) {
   return rigid_active(s) && (build || !s->rxn_valid);
 }
 
+// Whether the pair kernel of a step's first pass updates its particles, too:
+// without active spheres nothing else comes between, and these kernels gain by
+// it; not while a kernel is being timed, so that the figures stay those of
+// the separate kernels.
+bool pairs_update(const sdpdem_system* s) {
+  return !rigid_active(s) && !s->stress && s->prof_kernel == SDPDEM_K_NONE &&
+         forces_can_update(s->d, s->noise);
+}
+
 // (a5)-(a9): one force evaluation (Alg. 2) and, if asked, the update; fill
 // as needs_fill said before the pass's pass_prep.
 void run_pass(sdpdem_system* s, int velver, int commit, bool integrate, bool fill,
@@ -840,9 +849,12 @@ void run_pass(sdpdem_system* s, int velver, int commit, bool integrate, bool fil
     s->gather_ok = issue_rigid(s, fk ? s->side : st, fk, commit);
   }
   s->rigid_issued = false;
+  // a captured graph never reads the moved flag: no need to raise it
+  const bool track = d.reuse && !s->capturing;
+  const bool updated = integrate && velver == 1 && pairs_update(s);
   {
     Prof pr(s, SDPDEM_K_FLUID_FORCES, st, true);
-    launch_fluid_forces(d, s->noise, st, pr.t0(), pr.t1());
+    launch_fluid_forces(d, s->noise, updated, track, st, pr.t0(), pr.t1());
   }
   if (act) {
     if (fk && (!s->gather_ok || hipStreamWaitEvent(st, s->ev_gather, 0) != hipSuccess))
@@ -876,12 +888,10 @@ void run_pass(sdpdem_system* s, int velver, int commit, bool integrate, bool fil
   } else {
     d.have_rxn = 0;
   }
-  if (integrate) {
+  if (integrate && !updated) {
     Prof pr(s, SDPDEM_K_INTEGRATE, st);
     // the second pass of a step also advances the device step counter
-    // a captured graph never reads the moved flag: no need to raise it
-    launch_integrate(d, velver, act ? 1 : 0, velver == 2, act && !s->dense,
-                     d.reuse && !s->capturing, st);
+    launch_integrate(d, velver, act ? 1 : 0, velver == 2, act && !s->dense, track, st);
   }
 }
 

@@ -565,6 +565,133 @@ __device__ inline int block_exclusive_scan(int v, int* lds, int* total) {
   return res;
 }
 
+// ---- the first update of a step (Alg. 1) at the end of a pair kernel: the
+// arithmetic of the update kernel, rounded alike (that kernel keeps a text of
+// its own: through these functions its drift variants spill and take 6 %
+// longer)
+
+// v += hdt F / m (the mass rides in v.w; spins likewise)
+__device__ __forceinline__ void kick(D4& v, const double F[3], double hdt) {
+#pragma clang fp contract(off)
+  v.x = v.x + hdt * F[0] / v.w;
+  v.y = v.y + hdt * F[1] / v.w;
+  v.z = v.z + hdt * F[2] / v.w;
+}
+
+// the drift of p with velocity v and the boundary treatment of both
+__device__ __forceinline__ void drift(const Dev& d, const BoxD& B, D4& p, D4& v, int& bad) {
+#pragma clang fp contract(off)
+  double x[3] = {__builtin_fma(d.dt, v.x, p.x), __builtin_fma(d.dt, v.y, p.y),
+                 __builtin_fma(d.dt, v.z, p.z)};
+  double vv[3] = {v.x, v.y, v.z};
+  if (B.le) {
+    // through a sheared z face: re-enter as the image of the next box
+    if (x[2] < B.org[2]) {
+      x[2] += B.L[2];
+      x[0] += B.le_next;
+      vv[0] += B.le_jump;
+    } else if (x[2] >= B.org[2] + B.L[2]) {
+      x[2] -= B.L[2];
+      x[0] -= B.le_next;
+      vv[0] -= B.le_jump;
+    }
+    if (x[0] < B.org[0])
+      x[0] += B.L[0];
+    else if (x[0] >= B.org[0] + B.L[0])
+      x[0] -= B.L[0];
+  }
+  bool hit = false;  // a wall face was crossed in this drift
+  for (int a = 0; a < 3; ++a) {
+    double lo = B.org[a], hi = B.org[a] + B.L[a];
+    if (B.per[a]) {
+      if (x[a] < lo)
+        x[a] += B.L[a];
+      else if (x[a] >= hi)
+        x[a] -= B.L[a];
+    } else if (x[a] < lo || x[a] > hi) {
+      x[a] = x[a] < lo ? 2.0 * lo - x[a] : 2.0 * hi - x[a];
+      hit = true;
+      if (!d.noslip) vv[a] = -vv[a];  // slip: the normal component
+      if (x[a] < lo || x[a] > hi) bad |= ST_OUT_OF_DOMAIN;
+    }
+  }
+  // no-slip: the whole velocity reversed once, also at an edge or corner
+  if (hit && d.noslip) {
+    vv[0] = -vv[0];
+    vv[1] = -vv[1];
+    vv[2] = -vv[2];
+  }
+  p.x = x[0];
+  p.y = x[1];
+  p.z = x[2];
+  v.x = vv[0];
+  v.y = vv[1];
+  v.z = vv[2];
+}
+
+// Raises the flag of candidate reuse for a particle drifted to p, skin/2 or
+// more from where the last search saw it (one atomic per wave).
+__device__ __forceinline__ void raise_moved(const Dev& d, const BoxD& B, int i, const D4& p) {
+  const D4 q = d.xref[i];
+  double ex = p.x - q.x, ey = p.y - q.y, ez = p.z - q.z;
+  bool far;
+  if (B.le) {
+    // sheared: the displacement through the images of the drifted
+    // positions, less the flow's x displacement since the search at the
+    // reference height; two partners' separations then change by at most
+    // twice that plus shear_reach ts, which must stay below skin (ts the
+    // time between the searched positions and these: across a sheared
+    // face the image offset moved by the rate times L_z ts)
+    Geo G = geo_of(B);
+    G.le_shift = B.le_next;
+    min_img_box(G, ex, ey, ez);
+    const double ts = (double)(d.dstep[0] - d.sstep[0]) * d.dt;
+    ex -= B.shear * (q.z - (B.org[2] + 0.5 * B.L[2])) * ts;
+    const double lim = (d.pad - 0.5 * B.shear_reach * ts) * (1.0 - 1e-9);
+    far = !(lim > 0.0) || r2_exact(ex, ey, ez) > lim * lim;
+  } else {
+    min_img_box(geo_of(B), ex, ey, ez);
+    far = r2_exact(ex, ey, ez) > d.mv2;
+  }
+  const unsigned long long m = __ballot(far);
+  if (m && (threadIdx.x & 63) == (unsigned)(__ffsll((long long)m) - 1)) atomicOr(d.moved, 1);
+}
+
+// The first half-kick and the drift of particle i of type t (no active
+// spheres: a rigid particle stays) from its pair sums f (F, then the torque).
+__device__ __forceinline__ void first_update(const Dev& d, int track, const BoxD& B, int i,
+                                             uint8_t t, const float f[6]) {
+#pragma clang fp contract(off)
+  if (t != T_FLUID && t != T_INNER) return;
+  D4 v = d.vel[i], w = d.om[i], p = d.pos[i];
+  double sg = 1.0;
+  if (d.gtype == 1) {
+    const double x = d.gaxis == 0 ? p.x : (d.gaxis == 1 ? p.y : p.z);
+    sg = (x - B.org[d.gaxis] >= 0.5 * B.L[d.gaxis]) ? 1.0 : -1.0;
+  }
+  double F[3], N[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    F[a] = (double)f[a] + v.w * d.body[a] * sg;
+    N[a] = (double)f[3 + a];
+  }
+  const double hdt = 0.5 * d.dt;
+  kick(v, F, hdt);
+  kick(w, N, hdt);
+  int bad = 0;
+  if (t == T_FLUID) {
+    drift(d, B, p, v, bad);
+    d.pos[i] = p;
+  }
+  if (!isfinite(v.x) || !isfinite(v.y) || !isfinite(v.z) || !isfinite(w.x) || !isfinite(w.y) ||
+      !isfinite(w.z) || !isfinite(p.x) || !isfinite(p.y) || !isfinite(p.z))
+    bad |= ST_NONFINITE;
+  if (bad) atomicOr(d.status, bad);
+  d.vel[i] = v;
+  d.om[i] = w;
+  if (track && t == T_FLUID) raise_moved(d, B, i, p);
+}
+
 // a ^ b ^ c in one instruction (the compiler emits two)
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
   return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);

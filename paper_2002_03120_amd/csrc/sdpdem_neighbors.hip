@@ -785,7 +785,7 @@ __device__ __forceinline__ float add_rounded(float a, float b) {
 }
 
 template <bool STRESS>
-__global__ __launch_bounds__(BS) void k_fluid_forces(Dev d) {
+__global__ __launch_bounds__(BS) void k_fluid_forces(Dev d, int) {
   int i;
   const int b = blk_box<true>(d, i);
   if (b < 0) return;
@@ -840,8 +840,8 @@ __global__ __launch_bounds__(BS) void k_fluid_forces(Dev d) {
 // A quad's record lies in LDS in the quarters' order q ^ t (t: which of its
 // lanes wants it), which spreads the lanes' reads over the banks.  WIDE_OFS:
 // byte offsets into the records need more than 32 bits.
-template <bool STRESS, bool WIDE_OFS>
-__global__ __launch_bounds__(BS) void k_fluid_forces_thermal(Dev d) {
+template <bool STRESS, bool WIDE_OFS, bool UPDATE>
+__global__ __launch_bounds__(BS) void k_fluid_forces_thermal(Dev d, int track) {
   __shared__ __attribute__((aligned(64))) char stage[BS * sizeof(PR)];
   int i;
   const int b = blk_box<true>(d, i);
@@ -916,6 +916,10 @@ __global__ __launch_bounds__(BS) void k_fluid_forces_thermal(Dev d) {
   acc[3] *= -d.leverf;
   acc[4] *= -d.leverf;
   acc[5] *= -d.leverf;
+  if (UPDATE) {
+    first_update(d, track, B, i, ti, acc);
+    return;
+  }
   const size_t np = (size_t)d.npad;
   float* const o = d.fout;
 #pragma unroll
@@ -925,8 +929,8 @@ __global__ __launch_bounds__(BS) void k_fluid_forces_thermal(Dev d) {
 
 // the same with G lanes per particle: the lanes' pair terms pass through
 // LDS and lane q of the group adds component q over the slots in order
-template <int G, bool NOISE, bool STRESS>
-__global__ __launch_bounds__(BS) void k_fluid_forces_wide(Dev d) {
+template <int G, bool NOISE, bool STRESS, bool UPDATE>
+__global__ __launch_bounds__(BS) void k_fluid_forces_wide(Dev d, int track) {
   constexpr int NT = STRESS ? 10 : 9, PER = (NT + G - 1) / G;
   constexpr int ST = 12;                  // floats of a lane's row (16-byte stores)
   __shared__ __align__(16) float xch[BS * ST];
@@ -936,8 +940,9 @@ __global__ __launch_bounds__(BS) void k_fluid_forces_wide(Dev d) {
   const BoxD& B = d.boxes[b];
   const int g = (int)threadIdx.x % G;
   const int i = i0 + (int)threadIdx.x / G;
-  if (i >= B.first + B.count) return;
-  const uint8_t ti = d.type[i];
+  const int last = B.first + B.count;
+  if (!UPDATE && i >= last) return;
+  const uint8_t ti = i < last ? d.type[i] : (uint8_t)T_OUTER;
   float acc[PER];
 #pragma unroll
   for (int m = 0; m < PER; ++m) acc[m] = 0.0f;
@@ -970,48 +975,78 @@ __global__ __launch_bounds__(BS) void k_fluid_forces_wide(Dev d) {
     }
   }
   const size_t np = (size_t)d.npad;
+  if (UPDATE) __syncthreads();  // the exchange rows are free
 #pragma unroll
   for (int p = 0; p < PER; ++p) {
     const int q = p * G + g;
     if (q >= NT) continue;
     if (q >= 3 && q < 6) acc[p] *= -d.leverf;
-    d.fout[(q < 9 ? q : 12) * np + i] = acc[p];
+    if (UPDATE)
+      xch[((int)threadIdx.x / G) * ST + q] = acc[p];
+    else
+      d.fout[(q < 9 ? q : 12) * np + i] = acc[p];
+  }
+  if (UPDATE) {
+    // on full lanes
+    __syncthreads();
+    const int k = i0 + (int)threadIdx.x;
+    if ((int)threadIdx.x < BS / G && k < last)
+      first_update(d, track, B, k, d.type[k], xch + threadIdx.x * ST);
   }
 }
 
-template <int G>
-static auto forces_lanes(const Dev& d, bool noise) {
-  return noise ? (d.stress ? k_fluid_forces_wide<G, true, true>
-                           : k_fluid_forces_wide<G, true, false>)
-               : (d.stress ? k_fluid_forces_wide<G, false, true>
-                           : k_fluid_forces_wide<G, false, false>);
+// Where the kernel of a step's first pass also updates its particles (without
+// active spheres nothing else comes between, so the sums need not pass through
+// memory): the thermal kernel, whose arithmetic covers the update's memory
+// traffic (periodic box of 4.2 M particles, 514 + 210 us in two launches, 647
+// in one), and the several-lane kernels, where a launch less counts (8,000
+// particles 7.8 + 4.7 us, 8.9 in one).  Not the plain one-lane kernel (117 +
+// 55, 192 us: it waits on memory itself), and not a second pass, whose update
+// rewrites the pair records that the launch still reads (with a second array
+// of records 514 + 237, 776 us).
+static int forces_lanes_count(const Dev& d, bool noise) {
+  return lanes_per_particle(d.nactive, noise ? THERMAL4_MAX : ROWS4_MAX);
+}
+bool forces_can_update(const Dev& d, bool noise) {
+  return noise || forces_lanes_count(d, noise) > 1;
 }
 
-void launch_fluid_forces(const Dev& d, bool noise, hipStream_t st, hipEvent_t t0,
-                         hipEvent_t t1) {
+template <int G, bool NOISE>
+static auto forces_lanes(const Dev& d, bool update) {
+  return d.stress ? k_fluid_forces_wide<G, NOISE, true, false>
+         : update ? k_fluid_forces_wide<G, NOISE, false, true>
+                  : k_fluid_forces_wide<G, NOISE, false, false>;
+}
+template <bool WIDE_OFS>
+static auto forces_thermal(const Dev& d, bool update) {
+  return d.stress ? k_fluid_forces_thermal<true, WIDE_OFS, false>
+         : update ? k_fluid_forces_thermal<false, WIDE_OFS, true>
+                  : k_fluid_forces_thermal<false, WIDE_OFS, false>;
+}
+
+void launch_fluid_forces(const Dev& d, bool noise, bool update, bool track, hipStream_t st,
+                         hipEvent_t t0, hipEvent_t t1) {
   auto k = d.stress ? k_fluid_forces<true> : k_fluid_forces<false>;
-  if (noise) {
-    const bool ofs64 = (size_t)d.npad * sizeof(PR) > (size_t)UINT32_MAX;
-    k = d.stress ? (ofs64 ? k_fluid_forces_thermal<true, true> : k_fluid_forces_thermal<true, false>)
-                 : (ofs64 ? k_fluid_forces_thermal<false, true>
-                          : k_fluid_forces_thermal<false, false>);
-  }
-  const int lanes = lanes_per_particle(d.nactive, noise ? THERMAL4_MAX : ROWS4_MAX);
+  const int lanes = forces_lanes_count(d, noise);
   if (lanes == 16)
-    k = forces_lanes<16>(d, noise);
+    k = noise ? forces_lanes<16, true>(d, update) : forces_lanes<16, false>(d, update);
   else if (lanes == 4)
-    k = forces_lanes<4>(d, noise);
+    k = noise ? forces_lanes<4, true>(d, update) : forces_lanes<4, false>(d, update);
+  else if (noise)
+    k = (size_t)d.npad * sizeof(PR) > (size_t)UINT32_MAX ? forces_thermal<true>(d, update)
+                                                         : forces_thermal<false>(d, update);
+  int moved = track ? 1 : 0;
   const unsigned nb = (unsigned)(d.nablk * lanes);
   if (t0 && t1) {
     // the dispatch itself stamps the two events (no marker packets around
     // the kernel, which would stall the stream)
     Dev arg = d;
-    void* args[] = {&arg};
+    void* args[] = {&arg, &moved};
     if (hipExtLaunchKernel(reinterpret_cast<const void*>(k), dim3(nb), dim3(BS), args, 0, st,
                            t0, t1, 0) == hipSuccess)
       return;
   }
-  k<<<nb, BS, 0, st>>>(d);
+  k<<<nb, BS, 0, st>>>(d, moved);
 }
 
 // neighbour columns k0..k0+kn-1 as ids (-1 past a row's end), for export

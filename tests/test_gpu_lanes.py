@@ -89,3 +89,38 @@ def test_bits_do_not_depend_on_the_waves_per_sphere(S, skin):
             for b in (0, copies // 2, copies - 1):
                 assert np.array_equal(v[b], ref[f][0]), (f, b)
         g.close()
+
+
+def _fluid(kind):
+    if kind == "shear":
+        p, parts, info = W.shear_cell(15, phi=0.0, kBT=4e-3, shear_rate=8e-2, seed=5)
+    elif kind == "thermal":  # driven both ways, half of the box each
+        p, parts, info = W.reverse_poiseuille((14, 15, 16), kBT=4e-2, g=1e-2, seed=3)
+    else:  # a column under gravity that strikes its walls, no noise
+        p, parts, info = W.dam_break(tank=(12, 11, 14), column=(12, 11, 9), n_rigid=0)
+        p = dict(p, noslip=int(kind == "noslip"), g=[2e-2, 1e-2, -5e-2])
+    kT = 2.0 if kind in ("slip", "noslip") else 4e-2  # fast enough to cross a wall
+    return p, W.perturb(parts, p, jitter=0.1, kT=kT, seed=9, spin=True), info
+
+
+@pytest.mark.parametrize("copies", [1, 12, 60])  # 16 lanes, 4, and (thermal) one
+@pytest.mark.parametrize("skin", [0.0, 0.2])
+@pytest.mark.parametrize("kind", ["shear", "thermal", "slip", "noslip"])
+def test_the_update_in_the_pair_kernel_keeps_the_bits(S, kind, skin, copies):
+    """Without spheres the pair kernel of a step's first pass updates its
+    particles; while the virial is accumulated, a kernel of its own does."""
+    cell = _fluid(kind)
+    p = dict(cell[0], cell_factor=0.55, skin=skin)
+    got = []
+    for stress in (False, True):
+        parts, boxes, box_of = W.stack_cells([cell] * copies)
+        print(f"[case] {kind} x {copies}, skin {skin}, stress {stress}", flush=True)
+        g = S.System(p, parts, boxes=boxes, box_of=box_of)
+        g.set_stress(stress)
+        assert g.step(25) == 0
+        got.append({f: g.read_field(f)
+                    for f in ("POS", "VEL", "ANGVEL", "DENS", "F_SDPD", "N_SDPD")})
+        got[-1]["searches"] = np.asarray(g.info()[14])
+        g.close()
+    for f, v in got[0].items():
+        assert np.array_equal(v, got[1][f]), f
