@@ -83,8 +83,21 @@ __global__ __launch_bounds__(BS) void k_bin(Dev d) {
   const int c = B.cell_off + (d.type[i] == T_OUTER ? B.wall_off : 0) + cell_index(B.g, cx, cy, cz);
   d.key[i] = (uint32_t)c;
   // the arrival order in the cell places the particle in the scatter (the
-  // cell sort then fixes the order inside the cell)
-  d.rank[i] = atomicAdd(&d.count[c], 1);
+  // permute then fixes the order inside the cell); one addition per run of
+  // lanes in the same cell, since additions to one word queue up in memory
+  // (eight particles per cell, 0.4 M in 16 boxes: 30 us by lane, 7.4 by run;
+  // one per cell: as before)
+  const int lane = (int)threadIdx.x & 63;
+  const bool head = lane == 0 || __shfl_up(c, 1, 64) != c;
+  const unsigned long long heads = __ballot(head), here = __ballot(true);
+  const int first = 63 - __clzll((long long)(heads & (~0ull >> (63 - lane))));
+  int rank = 0;
+  if (head) {
+    const unsigned long long stop =
+        lane == 63 ? 0ull : (heads | ~here) >> (lane + 1);
+    rank = atomicAdd(&d.count[c], stop ? __ffsll((long long)stop) : 64 - lane);
+  }
+  d.rank[i] = __shfl(rank, first, 64) + lane - first;
 }
 
 void launch_bin(const Dev& d, hipStream_t st) {
