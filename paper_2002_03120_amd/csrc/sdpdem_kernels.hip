@@ -466,8 +466,17 @@ __device__ __forceinline__ int wave_sum_i(int v) {
 // Worth it for up to about a thousand spheres with eight or more rounds each:
 // the sedimentation box 38 us (searching) and 26 us (replaying) with a wave,
 // 19 and 15 us so; 600 spheres of three to four rounds 16 and 8, 18 and 7 us.
+//
+// A replayed round waits once: all fields of a recorded partner (nearly
+// always within H_s) are read together, beside the next round's entries.
+// 64 shear cells 144 -> 130 us filling and 94 -> 86 us not, 20,000 spheres
+// in a million particles 54 -> 48 us (a further round of fields ahead takes
+// the registers of a wave: 91 and 52 us).  What remains is lines: some 46 a
+// round, each a miss, at the fifty or so that a CU keeps in flight.  Six
+// waves per SIMD, at a few spilled registers outside the loops: the search
+// of 13,800 spheres takes 49 us at five, 46 at six.
 template <bool STRESS, bool FILL, int W>
-__global__ __launch_bounds__(W == 1 ? BS : 64 * W) void k_fpi_action(Dev d, int use_rec) {
+__global__ __launch_bounds__(W == 1 ? BS : 64 * W) __attribute__((amdgpu_waves_per_eu(6))) void k_fpi_action(Dev d, int use_rec) {
   constexpr int NC = 8;  // Omega, sum w v (3), sum w F (3), sum w r_z
   static_assert(W == 1 || W == NC, "wave c adds component c");
   __shared__ double xch[W == 1 ? 1 : NC * W * 64];
@@ -493,8 +502,7 @@ __global__ __launch_bounds__(W == 1 ? BS : 64 * W) void k_fpi_action(Dev d, int 
   int nrig = 0;
   // the pair geometry of fluid candidate j: image separation, its z image
   // and r^2 (the same operations on both paths, so the sums agree bit for bit)
-  auto geom = [&](int j, double& ez, int& kz) {
-    const D4 pj = d.pos[j];
+  auto geom = [&](const D4& pj, double& ez, int& kz) {
     double ex = ps.x - pj.x, ey = ps.y - pj.y;
     ez = ps.z - pj.z;
     kz = min_img_box(G, ex, ey, ez);
@@ -502,27 +510,20 @@ __global__ __launch_bounds__(W == 1 ? BS : 64 * W) void k_fpi_action(Dev d, int 
   };
   // the terms of one coupled fluid particle, each rounded, added to acc (W = 1)
   // or left in t
-  auto couple = [&](int j, double r2, double ez, int kz, double* t) {
+  // (returns the reaction's weight)
+  auto couple = [&](const D4& vj, const float* fj, double r2, double ez, int kz, double* t) {
 #pragma clang fp contract(off)
     const double qh = sqrt(r2) * invH, omq = 1.0 - qh;
     const double pw = (1.0 + 3.0 * qh) * omq * omq * omq;
     const double wj = wnorm * pw;
-    if (FILL) {
-      // hand the pair to the reaction: one slot of j (the arrival order
-      // does not matter, the reaction sums its slots by sphere record)
-      const int slot = atomicAdd(&d.rxn_cnt[j], 1);
-      if (slot < RXN_CAP)
-        d.rxn_slot[(size_t)slot * np + j] = make_int2(wave, __float_as_int((float)pw));
-    }
-    const D4 vj = d.vel[j];
     const double term[NC] = {
         wj,
         wj * (vj.x + (double)kz * G.le_jump),  // image velocity (Lees-Edwards)
         wj * vj.y,
         wj * vj.z,
-        wj * (double)d.fout[6 * np + j],
-        wj * (double)d.fout[7 * np + j],
-        wj * (double)d.fout[8 * np + j],
+        wj * (double)fj[0],
+        wj * (double)fj[1],
+        wj * (double)fj[2],
         STRESS ? wj * ez : 0.0};  // the coupling's lever (z part)
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -531,6 +532,13 @@ __global__ __launch_bounds__(W == 1 ? BS : 64 * W) void k_fpi_action(Dev d, int 
       else
         t[W == 1 ? 0 : c] = term[c];
     }
+    return (float)pw;
+  };
+  // hand a pair to the reaction: one slot of j (the arrival order does not
+  // matter, the reaction sums its slots by sphere record)
+  auto hand = [&](int slot, int j, float pw) {
+    if (slot < RXN_CAP)
+      d.rxn_slot[(size_t)slot * np + j] = make_int2(wave, __float_as_int(pw));
   };
   // W > 1: the end of W rounds, every lane's terms (zeros without a pair)
   auto add = [&](const double* t) {
@@ -549,23 +557,37 @@ __global__ __launch_bounds__(W == 1 ? BS : 64 * W) void k_fpi_action(Dev d, int 
   int rounds = 0;  // candidate rounds of the cell search
   if (stored >= 0) {
     rounds = stored;
+    // the last round's slots are stored while a round's fields arrive (their
+    // counters travel to memory)
+    int en = w < stored ? list[w * 64 + lane] : -1;
+    int slot = RXN_CAP, js = 0;
+    float pw = 0.0f;
     for (int r = w; r - w < stored; r += W) {
-      const int e = r < stored ? list[r * 64 + lane] : -1;
+      const int e = en;
+      en = r + W < stored ? list[(r + W) * 64 + lane] : -1;
       double t[W == 1 ? 1 : NC] = {};
+      const int j = e >= 0 ? e : e == -1 ? si : -2 - e;
+      const D4 pj = d.pos[j], vj = d.vel[j];
+      const float fj[3] = {d.fout[6 * np + j], d.fout[7 * np + j], d.fout[8 * np + j]};
+      if (FILL) hand(slot, js, pw);
+      slot = RXN_CAP;
       if (e != -1) {
-        const int j = e >= 0 ? e : -2 - e;
         double ez;
         int kz;
-        const double r2 = geom(j, ez, kz);
+        const double r2 = geom(pj, ez, kz);
         if (r2 < H2) {
-          if (e >= 0)
-            couple(j, r2, ez, kz, t);
-          else
+          if (e >= 0) {
+            if (FILL) slot = atomicAdd(&d.rxn_cnt[j], 1);
+            js = j;
+            pw = couple(vj, fj, r2, ez, kz, t);
+          } else {
             ++nrig;
+          }
         }
       }
       add(t);
     }
+    if (FILL) hand(slot, js, pw);
   } else {
     const Grid gr = B.g;
     const int coff = B.cell_off;
@@ -632,13 +654,17 @@ __global__ __launch_bounds__(W == 1 ? BS : 64 * W) void k_fpi_action(Dev d, int 
           if (tj == T_FLUID || tj == T_RIGID) {
             double ez;
             int kz;
-            const double r2 = geom(j, ez, kz);
+            const double r2 = geom(d.pos[j], ez, kz);
             if (r2 < Hr2) rec = tj == T_RIGID ? -2 - j : j;
             if (r2 < H2) {
               if (tj == T_RIGID)
                 ++nrig;
-              else
-                couple(j, r2, ez, kz, tm);
+              else {
+                const float fj[3] = {d.fout[6 * np + j], d.fout[7 * np + j], d.fout[8 * np + j]};
+                const int slot = FILL ? atomicAdd(&d.rxn_cnt[j], 1) : 0;
+                const float pw = couple(d.vel[j], fj, r2, ez, kz, tm);
+                if (FILL) hand(slot, j, pw);
+              }
             }
           }
         }
