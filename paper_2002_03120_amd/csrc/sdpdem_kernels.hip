@@ -88,7 +88,8 @@ __global__ __launch_bounds__(BS) void k_bin(Dev d) {
   // (eight particles per cell, 0.4 M in 16 boxes: 30 us by lane, 7.4 by run;
   // one per cell: as before)
   const int lane = (int)threadIdx.x & 63;
-  const bool head = lane == 0 || __shfl_up(c, 1, 64) != c;
+  const int before = __shfl_up(c, 1, 64);  // all lanes: an idle one would read as 0
+  const bool head = lane == 0 || before != c;
   const unsigned long long heads = __ballot(head), here = __ballot(true);
   const int first = 63 - __clzll((long long)(heads & (~0ull >> (63 - lane))));
   int rank = 0;

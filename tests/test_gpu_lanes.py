@@ -124,3 +124,31 @@ def test_the_update_in_the_pair_kernel_keeps_the_bits(S, kind, skin, copies):
         g.close()
     for f, v in got[0].items():
         assert np.array_equal(v, got[1][f]), f
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 130, 700, 2000])
+@pytest.mark.parametrize("order", ["as drawn", "by x", "lane 1 in cell 0"])
+def test_binning_by_runs(S, n, order):
+    """Runs of equal cells within a wave, at its edges, and none at all: every
+    particle is found once, with the neighbours of the exact test."""
+    L, h = 8.0, 1.5
+    p, parts, _ = W.random_box(n, (L, L, L), (1, 1, 1), h=h, seed=n)
+    if order == "by x":
+        parts["pos"] = parts["pos"][np.lexsort(np.floor(parts["pos"] / 2.0).T[::-1])]
+    elif order == "lane 1 in cell 0":
+        parts["pos"][1::64] *= 1e-2
+    x = parts["pos"]
+    e = x[:, None] - x[None]
+    e -= L * np.round(e / L)
+    near = (e * e).sum(2) < h * h
+    np.fill_diagonal(near, False)
+    for cf in (0.55, 1.0):
+        print(f"[case] n={n}, {order}, cell factor {cf}", flush=True)
+        g = S.System(dict(p, cell_factor=cf, max_neighbors=160), parts)
+        g.compute_forces()
+        assert np.array_equal(g.read_field("POS").reshape(n, 3), x)
+        rows, cols = g.read_neighbors()
+        got = np.zeros_like(near)
+        got[np.repeat(np.arange(n), np.diff(rows)), cols] = True
+        assert np.array_equal(got, near) and len(cols) == near.sum()
+        g.close()
