@@ -416,7 +416,7 @@ void launch_rigid_gather(const Dev& d, hipStream_t st) {
 // (a6) fluid-particle action: one wavefront per rigid particle gathers the
 // fluid inside H_s = R_s + h (Sec. 2.4): Omega_s, the W-weighted fluid
 // velocity, the W-weighted F^C + F^D of the neighbours and the number of
-// other rigid centres inside H_s (k_fpi_finish then forms eps, F^DG and
+// other rigid centres inside H_s (finish_sphere then forms eps, F^DG and
 // F^PG from them).  The cell rows of the search box are contiguous slices
 // of the sorted arrays; the wave walks their concatenation with one
 // candidate per lane.  With FILL it also hands every coupled fluid particle
@@ -429,13 +429,58 @@ void launch_rigid_gather(const Dev& d, hipStream_t st) {
 // every lane summing the same terms in the same order (a sphere whose
 // search needed more rounds than the record holds searches again).
 
-__device__ double drag_b(double eps, double dv, double dd, double rho, double mu) {
+__device__ __forceinline__ double drag_b(double eps, double dv, double dd, double rho,
+                                         double mu) {
+#pragma clang fp contract(off)
   // beta / (1 - eps) of the Ergun (eps <= 0.8) and Wen-Yu branches
   if (eps <= 0.8) return 150.0 * mu * (1.0 - eps) / (eps * dd * dd) + 1.75 * rho * dv / dd;
   double re = rho * dd * eps * dv / mu;
   double cd_dv = re <= 1000.0 ? 24.0 * mu * (1.0 + 0.15 * pow(re, 0.687)) / (rho * dd * eps)
                               : 0.44 * dv;
   return 0.75 * cd_dv * eps * rho * pow(eps, -2.65) / dd;
+}
+
+// (a6, second half) eps, F^DG and F^PG of sphere s (wave t of the action,
+// particle si of velocity vs) from the sums a of its action.
+template <bool STRESS>
+__device__ __forceinline__ void finish_sphere(const Dev& d, int t, int s, double R, const D4& vs,
+                                              const double* a, int nrig) {
+#pragma clang fp contract(off)
+  const double H = R + d.h;
+  const double invH = 1.0 / H, wnorm = 105.0 / (16.0 * PI * H * H * H);  // Eq. kernel
+  const double om = a[0], v0 = a[1], v1 = a[2], v2 = a[3], f0 = a[4], f1 = a[5], f2 = a[6];
+  const double Vs = 4.0 / 3.0 * PI * R * R * R;
+  const double VH = 4.0 / 3.0 * PI * H * H * H;
+  double eps = 1.0 - Vs * (double)nrig / VH;
+  eps = fmin(fmax(eps, d.eps_min), 1.0);
+  d.eps[s] = eps;
+  d.omega[s] = om;
+  double dg[3] = {0, 0, 0}, pg[3] = {0, 0, 0};
+  if (om > 0.0) {
+    double dv[3] = {vs.x - v0 / om, vs.y - v1 / om, vs.z - v2 / om};
+    double dva = sqrt(dv[0] * dv[0] + dv[1] * dv[1] + dv[2] * dv[2]);
+    double B_ = drag_b(eps, dva, 2.0 * R, d.rho0, d.eta);
+    double kp = d.rho0 * Vs / d.m_f;
+    for (int k = 0; k < 3; ++k) dg[k] = -B_ * Vs * dv[k];
+    pg[0] = kp * (f0 / om);
+    pg[1] = kp * (f1 / om);
+    pg[2] = kp * (f2 / om);
+  }
+  for (int k = 0; k < 3; ++k) {
+    d.f_dg[3 * s + k] = dg[k];
+    d.f_pg[3 * s + k] = pg[k];
+  }
+  // virial of the coupling: lever (sum_j w_sj r_sj / Omega_s)_z times the
+  // x force (the contacts keep theirs beside it)
+  if (STRESS) d.wzx_r[2 * s] = om > 0.0 ? (a[7] / om) * (dg[0] + pg[0]) : 0.0;
+  // F^DG / Omega times the kernel's normalisation beside the sphere's
+  // cell-ordered record, with 1/H_s (0: the sphere couples to nothing)
+  D4 rc;
+  rc.x = om > 0.0 ? dg[0] / om * wnorm : 0.0;
+  rc.y = om > 0.0 ? dg[1] / om * wnorm : 0.0;
+  rc.z = om > 0.0 ? dg[2] / om * wnorm : 0.0;
+  rc.w = om > 0.0 ? invH : 0.0;
+  d.rdg_c[t] = rc;
 }
 
 __device__ __forceinline__ double wave_sum(double v) {
@@ -482,6 +527,7 @@ __global__ __launch_bounds__(W == 1 ? BS : 64 * W) __attribute__((amdgpu_waves_p
   static_assert(W == 1 || W == NC, "wave c adds component c");
   __shared__ double xch[W == 1 ? 1 : NC * W * 64];
   __shared__ int xrig[W];
+  __shared__ double xsum[W == 1 ? 1 : NC];
   const int wave = W == 1 ? xcd_wave() : (int)blockIdx.x;
   const int lane = threadIdx.x & 63;
   const int w = W == 1 ? 0 : (int)(threadIdx.x >> 6);
@@ -492,6 +538,8 @@ __global__ __launch_bounds__(W == 1 ? BS : 64 * W) __attribute__((amdgpu_waves_p
   const BoxD& B = d.boxes[__builtin_amdgcn_readfirstlane(d.rbox[s])];
   const Geo G = geo_of(B);
   const D4 ps = d.pos[si];
+  D4 vs;
+  if (W > 1) vs = d.vel[si];
   const double R = ps.w, H = R + d.h, H2 = H * H;
   const double invH = 1.0 / H, wnorm = 105.0 / (16.0 * PI * H * H * H);  // Eq. kernel
   const size_t np = (size_t)d.npad;
@@ -681,20 +729,28 @@ __global__ __launch_bounds__(W == 1 ? BS : 64 * W) __attribute__((amdgpu_waves_p
   for (int c = 0; c < (W == 1 ? NC : 1); ++c)
     if (STRESS || W > 1 || c < 7) acc[c] = wave_sum(acc[c]);
   if (W > 1) {
-    if (lane == 0) xrig[w] = nrig;
+    if (lane == 0) {
+      xrig[w] = nrig;
+      xsum[w] = acc[0];
+    }
     __syncthreads();
+    if (w != 0) return;
   }
   if (lane != 0) return;
-  double* const out = d.act_sum + 8 * (size_t)wave;
+  double sums[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) sums[c] = W > 1 ? xsum[W > 1 ? c : 0] : acc[W > 1 ? 0 : c];
   if (W > 1) {
-    out[w] = acc[0];
-    if (w != 0) return;
     nrig = 0;
 #pragma unroll
     for (int k = 0; k < W; ++k) nrig += xrig[k];
+  }
+  if (W > 1) {
+    finish_sphere<STRESS>(d, wave, s, R, vs, sums, nrig);
   } else {
+    double* const out = d.act_sum + 8 * (size_t)wave;
 #pragma unroll
-    for (int c = 0; c < (W == 1 ? NC : 1); ++c) out[c] = acc[c];
+    for (int c = 0; c < NC; ++c) out[c] = sums[c];
   }
   // the record of this search (-1: more rounds than it holds, search
   // again) and the rigid count of this pass, for the finishing kernel
@@ -708,54 +764,20 @@ __global__ __launch_bounds__(W == 1 ? BS : 64 * W) __attribute__((amdgpu_waves_p
     d.act_meta[s] = make_int2(FILL && !use_rec && rounds <= ACT_ROUNDS ? rounds : -1, nrig);
 }
 
-// (a6, second half) one thread per sphere, in cell order: eps, F^DG and
-// F^PG from the sums its action wave left (the per-sphere FP64 algebra,
-// divisions and powers, runs here with every lane busy instead of on one
-// lane of each action wave)
+// After the action with a wave per sphere, one thread per sphere, in cell
+// order: the per-sphere FP64 algebra, divisions and powers, runs here with
+// every lane busy instead of on one lane of each action wave (13,800 spheres
+// 46 + 5.2 us, 61 us in one; 600 spheres 15.5 + 5.0 and 21).  A workgroup
+// per sphere, that is of few spheres, does it at its end: a launch less, and
+// 1.6 us more (the sedimentation box: 18.4 + 4.4 us, 20.2).
 template <bool STRESS>
 __global__ __launch_bounds__(BS) void k_fpi_finish(Dev d) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= d.nr) return;
   const int s = d.ritems[t];
   const int si = d.rig_sorted[s];
-  const double R = d.pos[si].w, H = R + d.h;
-  const double invH = 1.0 / H, wnorm = 105.0 / (16.0 * PI * H * H * H);  // Eq. kernel
-  const double* a = d.act_sum + 8 * (size_t)t;
-  const double om = a[0], v0 = a[1], v1 = a[2], v2 = a[3], f0 = a[4], f1 = a[5], f2 = a[6];
-  const int nrig = d.act_meta[s].y;
-  const double Vs = 4.0 / 3.0 * PI * R * R * R;
-  const double VH = 4.0 / 3.0 * PI * H * H * H;
-  double eps = 1.0 - Vs * (double)nrig / VH;
-  eps = fmin(fmax(eps, d.eps_min), 1.0);
-  d.eps[s] = eps;
-  d.omega[s] = om;
-  double dg[3] = {0, 0, 0}, pg[3] = {0, 0, 0};
-  if (om > 0.0) {
-    const D4 vs = d.vel[si];
-    double dv[3] = {vs.x - v0 / om, vs.y - v1 / om, vs.z - v2 / om};
-    double dva = sqrt(dv[0] * dv[0] + dv[1] * dv[1] + dv[2] * dv[2]);
-    double B_ = drag_b(eps, dva, 2.0 * R, d.rho0, d.eta);
-    double kp = d.rho0 * Vs / d.m_f;
-    for (int k = 0; k < 3; ++k) dg[k] = -B_ * Vs * dv[k];
-    pg[0] = kp * (f0 / om);
-    pg[1] = kp * (f1 / om);
-    pg[2] = kp * (f2 / om);
-  }
-  for (int k = 0; k < 3; ++k) {
-    d.f_dg[3 * s + k] = dg[k];
-    d.f_pg[3 * s + k] = pg[k];
-  }
-  // virial of the coupling: lever (sum_j w_sj r_sj / Omega_s)_z times the
-  // x force (the contacts keep theirs beside it)
-  if (STRESS) d.wzx_r[2 * s] = om > 0.0 ? (a[7] / om) * (dg[0] + pg[0]) : 0.0;
-  // F^DG / Omega times the kernel's normalisation beside the sphere's
-  // cell-ordered record, with 1/H_s (0: the sphere couples to nothing)
-  D4 rc;
-  rc.x = om > 0.0 ? dg[0] / om * wnorm : 0.0;
-  rc.y = om > 0.0 ? dg[1] / om * wnorm : 0.0;
-  rc.z = om > 0.0 ? dg[2] / om * wnorm : 0.0;
-  rc.w = om > 0.0 ? invH : 0.0;
-  d.rdg_c[t] = rc;
+  finish_sphere<STRESS>(d, t, s, d.pos[si].w, d.vel[si], d.act_sum + 8 * (size_t)t,
+                        d.act_meta[s].y);
 }
 
 template <int W>
@@ -766,10 +788,11 @@ static auto action_kernel(const Dev& d, bool fill) {
 
 void launch_fpi_action(const Dev& d, bool fill, bool use_rec, hipStream_t st) {
   if (d.nr == 0) return;
-  if (d.act_wide)
+  if (d.act_wide) {
     action_kernel<8>(d, fill)<<<d.nr, 512, 0, st>>>(d, use_rec ? 1 : 0);
-  else
-    action_kernel<1>(d, fill)<<<nblocks((size_t)d.nr * 64), BS, 0, st>>>(d, use_rec ? 1 : 0);
+    return;
+  }
+  action_kernel<1>(d, fill)<<<nblocks((size_t)d.nr * 64), BS, 0, st>>>(d, use_rec ? 1 : 0);
   // one wavefront per block: the few thousand threads of the finish spread
   // over as many CUs as possible (its FP64 divisions and powers are latency)
   auto f = d.stress ? k_fpi_finish<true> : k_fpi_finish<false>;
