@@ -708,8 +708,12 @@ __device__ __forceinline__ float sqrtf_nr(float x) {
 }
 
 // -2 ln(u) for u in [2^-24, 1] from the hardware log2, the product with
-// -2 ln 2 carried to twice the precision
+// -2 ln 2 carried to twice the precision (no contraction: t must be the
+// rounded product whose error the inner operation finds).  Over every u its
+// square root below errs by at most 1.28e-7, 3.49e-8 in the mean square (the
+// library's logarithm and square root: 1.49e-7 and 3.77e-8).
 __device__ __forceinline__ float minus_2_log(float u) {
+#pragma clang fp contract(off)
   constexpr float hi = -1.3862943611198906f;
   constexpr float lo = (float)(-1.3862943611198906188 - (double)hi);
   const float l = __builtin_amdgcn_logf(u);
