@@ -45,7 +45,9 @@ def pair_kernel_bytes(n, n_act, nnz_act, noise):
 # device helpers the pair kernel calls (hashed with it; the rest of their
 # header does not change the kernel)
 PAIR_KERNEL_HELPERS = ("xcd_tid", "logical_block", "blk_box", "geo_of", "min_img_box",
-                       "min_img_fast", "load_pr", "philox10", "u01", "pair_normals")
+                       "min_img_fast", "load_pr", "xor3", "sqrtf_nr", "minus_2_log", "philox10",
+                       "u01", "pair_normals", "wave_lds_sync", "load_to_lds16", "wait_loads",
+                       "wait_lds")
 
 
 def _function_text(src, name):
