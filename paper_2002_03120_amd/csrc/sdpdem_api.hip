@@ -569,6 +569,10 @@ void fill_constants(sdpdem_system* s, const Sizes& z) {
   for (const BoxD& B : z.boxes) d.any_le |= B.le;
   d.maxcand = z.maxcand;
   d.hc = P.h + P.skin;
+  // a row's reach grows with the radius: h + skin covers the plain search
+  d.short_x = 0;
+  for (const BoxD& B : z.boxes)
+    d.short_x |= search_axis_short(B.g, B.le, reach_cells(B.g, d.hc)) ? 1 : 0;
   d.hc2 = d.hc * d.hc;
   d.pad = d.reuse ? 0.5 * P.skin : 0.0;
   // a partner within h now was within h + 2 (skin/2) of it at the search;

@@ -3,6 +3,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstddef>
 #include <cstdint>
 
@@ -62,6 +63,22 @@ struct Grid {
   int per[3];
   int ncells;
 };
+
+// cells each way that hold every point within H of a cell's points
+__host__ __device__ __forceinline__ int reach_cells(const Grid& g, double H) {
+  int k = 1;
+  for (int a = 0; a < 3; ++a) {
+    const int c = (int)ceil(H * g.inv_cs[a] * (1.0 + 1e-9));
+    k = c > k ? c : k;
+  }
+  return k;
+}
+
+// Whether a row of reach k can take a periodic x axis whole: it spans at most
+// 2k + 1 cells, seen through a sheared face 2k + 3 and one more by rounding.
+__host__ __device__ __forceinline__ bool search_axis_short(const Grid& g, int le, int k) {
+  return g.per[0] && g.nc[0] <= 2 * k + (le ? 4 : 1);
+}
 
 // One box of a batch: an independent domain with its own periodic or wall
 // axes, optional Lees-Edwards shear (flow x, gradient z), thermal energy and
@@ -162,6 +179,7 @@ struct Dev {
   // than skin/2 from them
   int reuse;
   int any_le;      // some box is sheared
+  int short_x;     // in some box a row of the search can take the x axis whole
   int maxcand;
   double hc, hc2;  // h + skin and its square
   double pad;      // skin/2: how far a particle may be from its cell

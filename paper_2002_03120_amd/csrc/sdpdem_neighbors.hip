@@ -168,13 +168,7 @@ __device__ __forceinline__ void build_density(const Dev& d, int after_drift) {
     cells(k0, k1);
     if (woff) cells(k0 + woff, k1 + woff);
   };
-  // cells of R or more: the whole 27-cell stencil (lanes of a cell walk the
-  // same runs in step); smaller cells: the rows and x cells within R only
-  const int kr = reach_cells(gr, R);
-  if (kr == 1)
-    for_stencil<false>(G, gr, coff, pi.x, pi.y, pi.z, R, cc, 1, run);
-  else
-    for_stencil_pruned(G, gr, coff, pi.x, pi.y, pi.z, R, cc, kr, run);
+  for_search(G, gr, coff, pi.x, pi.y, pi.z, R, cc, reach_cells(gr, R), run);
   if (cnt > d.maxn || (CAND && ccnt > d.maxcand)) {
     atomicOr(d.status, ST_NBR_OVERFLOW);
     cnt = min(cnt, d.maxn);
@@ -201,7 +195,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(5))) void k_
 // row of the stencil (its geometry and cell starts, which the one-lane walk
 // loads one after the other), then the lanes take the candidates of the
 // concatenated rows G at a time; ballots give the slots in candidate order.
-template <int G, bool CAND>
+template <int G, bool CAND, bool EXACT>
 __device__ __forceinline__ void build_density_wide(const Dev& d, int after_drift) {
   __shared__ double sums[BS / G];
   __shared__ double2 xch[BS];
@@ -231,10 +225,8 @@ __device__ __forceinline__ void build_density_wide(const Dev& d, int after_drift
     const int kr = reach_cells(gr, R);
     const StencilShape sh_ = stencil_shape(gr, cc, kr);
     const int nrows = sh_.zn * sh_.yn;
-    // single-precision rows where they hold (the candidate search has no
-    // registers to spare for them: 43 -> 50 us on 83,000 particles)
     PlainRows rows = {};
-    if (!CAND) rows = plain_rows(geo, gr, pi.x, pi.y, pi.z, R, cc, kr);
+    if (!CAND || EXACT) rows = plain_rows(geo, gr, pi.x, pi.y, pi.z, R, cc, kr);
     const float inv_yn = 1.0f / (float)sh_.yn;
     double acc = d.W0;
     int cnt = 0, ccnt = 0;
@@ -252,11 +244,8 @@ __device__ __forceinline__ void build_density_wide(const Dev& d, int after_drift
         // row / yn without an integer division: (row + 1/2) / yn stays at
         // least 1 / (2 yn) away from every integer
         const int zi = (int)(((float)(rb + g) + 0.5f) * inv_yn), yi = rb + g - zi * sh_.yn;
-        if (!CAND && rows.plain)
-          plain_row(rows, gr, coff, cc, kr, zi - kr, yi - kr, a0, a1, b0, b1);
-        else
-          stencil_row_zy<true>(geo, gr, coff, pi.x, pi.y, pi.z, R, cc, kr, sh_, sh_.zlo + zi,
-                               sh_.ylo + yi, a0, a1, b0, b1);
+        search_row<!CAND, EXACT>(geo, gr, coff, pi.x, pi.y, pi.z, R, cc, kr, sh_, rows, zi, yi, a0,
+                                 a1, b0, b1);
         if (a1 > a0) {
           s0 = d.cstart[a0];
           e0 = d.cstart[a1] - s0;
@@ -356,22 +345,27 @@ __device__ __forceinline__ void build_density_wide(const Dev& d, int after_drift
 }
 
 // (seven waves per SIMD pay in the larger systems that take four lanes)
-template <int G>
+template <int G, bool EXACT>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(G == 4 ? 7 : 5))) void
 k_build_density_wide(Dev d) {
-  build_density_wide<G, false>(d, 0);
+  build_density_wide<G, false, EXACT>(d, 0);
 }
-template <int G>
+template <int G, bool EXACT>
 __global__ __launch_bounds__(BS) void k_build_candidates_wide(Dev d, int after_drift) {
-  build_density_wide<G, true>(d, after_drift);
+  build_density_wide<G, true, EXACT>(d, after_drift);
 }
 
 template <int G>
 static void build_density_lanes(const Dev& d, bool cand, int after_drift, hipStream_t st) {
-  if (cand)
-    k_build_candidates_wide<G><<<d.nblk * G, BS, 0, st>>>(d, after_drift);
+  const int nb = d.nblk * G;
+  if (cand && d.short_x)
+    k_build_candidates_wide<G, true><<<nb, BS, 0, st>>>(d, after_drift);
+  else if (cand)
+    k_build_candidates_wide<G, false><<<nb, BS, 0, st>>>(d, after_drift);
+  else if (d.short_x)
+    k_build_density_wide<G, true><<<nb, BS, 0, st>>>(d);
   else
-    k_build_density_wide<G><<<d.nblk * G, BS, 0, st>>>(d);
+    k_build_density_wide<G, false><<<nb, BS, 0, st>>>(d);
 }
 
 void launch_build_density(const Dev& d, bool cand, bool after_drift, hipStream_t st) {

@@ -66,6 +66,44 @@ def test_bits_do_not_depend_on_the_lanes_per_particle(S, kind, skin):
         g.close()
 
 
+def _narrow(kind, nx):
+    """A jittered box nx cells of 1.05 h across in x; walls in z for "walls"."""
+    h, L = 1.5, 1.5 * 1.05 * nx
+    p, parts, info = W.random_box(int(0.8 * L * 9.0 * 9.0), (L, 9.0, 9.0),
+                                  (1, 1, 0 if kind == "walls" else 1), h=h, seed=nx)
+    # late enough for the images across the sheared faces to be displaced
+    p = dict(p, kBT=4e-3, shear_rate=6e-2 if kind == "shear" else 0.0, itr_start=12345)
+    if kind == "walls":  # outer walls in every cell, binned behind the fluid
+        parts["type"][::9] = W.OUTER_WALL
+    return p, parts, info
+
+
+@pytest.mark.parametrize("skin", [0.0, 0.1])
+@pytest.mark.parametrize("kind,nx,cf", [("plain", 3, 1.0), ("plain", 4, 1.0), ("walls", 3, 1.0),
+                                        ("shear", 3, 1.0), ("shear", 4, 1.0), ("shear", 5, 1.0),
+                                        ("shear", 6, 1.0), ("plain", 3, 0.55), ("shear", 3, 0.55)])
+def test_bits_of_narrow_boxes(S, kind, nx, cf, skin):
+    """Rows of the search that take the x axis whole start at cell 0 in every
+    kernel: three to six cells across, of h or more (reach 1) and less."""
+    cell = _narrow(kind, nx)
+    p, n = dict(cell[0], cell_factor=cf, skin=skin), cell[1]["id"].shape[0]
+    assert n <= 1 << 14  # 16 lanes alone
+    ref = None
+    for total in (n, 60_000, 870_000 if kind == "shear" else 620_000):  # 16 lanes, 4, 1
+        copies = max(1, -(-total // n))
+        parts, boxes, box_of = W.stack_cells([cell] * copies)
+        print(f"[case] {kind}, {nx} cells, cell factor {cf}, skin {skin}, x {copies}", flush=True)
+        g = S.System(p, parts, boxes=boxes, box_of=box_of)
+        assert g.compute_forces() == 0
+        got, _ = _state(g, n, copies, False)
+        if ref is None:
+            ref = got
+        for f, v in got.items():
+            for b in (0, copies // 2, copies - 1):
+                assert np.array_equal(v[b], ref[f][0]), (f, b)
+        g.close()
+
+
 @pytest.mark.parametrize("skin", [0.0, 0.2])
 def test_bits_do_not_depend_on_the_waves_per_sphere(S, skin):
     """One large sphere per box, whose coupling takes some eighteen rounds of
