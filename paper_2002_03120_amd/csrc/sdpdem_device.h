@@ -237,8 +237,10 @@ __device__ __forceinline__ double slab_dist(double x, double lo, double cs) {
 }
 
 // the row at unwrapped z and y cell indices (zu, yu); every operation rounded
-// (no contraction), so that the same row comes out in every kernel
-template <bool PRUNE>
+// (no contraction), so that the same row comes out in every kernel.  ORDERED:
+// the cells of a pruned row in the order the whole row has them, which starts
+// at cell 0 where it takes the x axis whole.
+template <bool PRUNE, bool ORDERED = false>
 __device__ __forceinline__ void stencil_row_zy(const Geo& B, const Grid& G, int off, double px,
                                                double py, double pz, double R, const int cc[3],
                                                int k, const StencilShape& sh, int zu, int yu,
@@ -277,6 +279,7 @@ __device__ __forceinline__ void stencil_row_zy(const Geo& B, const Grid& G, int 
   const double rx = PRUNE ? sqrt(R * R - d2) * (1.0 + 1e-9) + 1e-9 * G.cs[0]
                           : (double)(k + 1) * G.cs[0];
   int x0, xn;
+  bool whole = 2 * k + 1 >= nx;
   if (B.le && sh.zall) {
     x0 = 0;
     xn = nx;
@@ -284,6 +287,12 @@ __device__ __forceinline__ void stencil_row_zy(const Geo& B, const Grid& G, int 
     // candidates sit around x - k_z delta (k_z = wz, 0 off the sheared faces)
     const double xc = (B.le && wz != 0) ? px - (double)wz * B.le_shift : px;
     int xa, xb;
+    if (ORDERED && B.le && wz != 0) {
+      const double far = (double)(k + 1) * G.cs[0];
+      whole = (int)floor((xc + far - G.lo[0]) * G.inv_cs[0]) -
+                  (int)floor((xc - far - G.lo[0]) * G.inv_cs[0]) + 1 >=
+              nx;
+    }
     if (!PRUNE && !(B.le && wz != 0)) {  // the plain stencil
       xa = cc[0] - k;
       xb = cc[0] + k;
@@ -326,7 +335,12 @@ __device__ __forceinline__ void stencil_row_zy(const Geo& B, const Grid& G, int 
     }
   } else {
     int lo = x0, hi = x0 + xn - 1;  // 0 <= lo < nx: at most one wrap
-    if (hi >= nx) {
+    if (ORDERED && whole && hi >= nx) {
+      a0 = rowkey;
+      a1 = rowkey + hi - nx + 1;
+      b0 = rowkey + lo;
+      b1 = rowkey + nx;
+    } else if (hi >= nx) {
       a0 = rowkey + lo;
       a1 = rowkey + nx;
       b0 = rowkey;
@@ -339,13 +353,13 @@ __device__ __forceinline__ void stencil_row_zy(const Geo& B, const Grid& G, int 
 }
 
 // row r of the stencil, z-major
-template <bool PRUNE>
+template <bool PRUNE, bool ORDERED = false>
 __device__ __forceinline__ void stencil_row(const Geo& B, const Grid& G, int off, double px,
                                             double py, double pz, double R, const int cc[3],
                                             int k, const StencilShape& sh, int r, int& a0,
                                             int& a1, int& b0, int& b1) {
-  stencil_row_zy<PRUNE>(B, G, off, px, py, pz, R, cc, k, sh, sh.zlo + r / sh.yn,
-                        sh.ylo + r % sh.yn, a0, a1, b0, b1);
+  stencil_row_zy<PRUNE, ORDERED>(B, G, off, px, py, pz, R, cc, k, sh, sh.zlo + r / sh.yn,
+                                 sh.ylo + r % sh.yn, a0, a1, b0, b1);
 }
 
 // the same cells as fn(first_key, end_key) over the runs, in row order;

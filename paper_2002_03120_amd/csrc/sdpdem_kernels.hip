@@ -801,8 +801,9 @@ void launch_fpi_action(const Dev& d, bool fill, bool use_rec, hipStream_t st) {
 
 // Calls fn(record, valid) for the spheres of the cells within R of point ps
 // in the rigid grid of box B, one per lane of the group and round, in cell
-// order; every lane of the group makes the same calls.
-template <class Fn>
+// order (ORDERED: the order of for_stencil<false>); every lane of the group
+// makes the same calls.
+template <bool ORDERED = false, class Fn>
 __device__ __forceinline__ void for_rigid_near(const Dev& d, const BoxD& B, const Geo& G,
                                                const D4& ps, double R, Fn&& fn) {
   const Grid gr = B.rg;
@@ -818,7 +819,8 @@ __device__ __forceinline__ void for_rigid_near(const Dev& d, const BoxD& B, cons
     int sa = 0, la = 0, sb = 0, lb = 0;
     if (rb + g < nrows) {
       int a0, a1, b0, b1;
-      stencil_row<true>(G, gr, coff, ps.x, ps.y, ps.z, R, cc, kr, sh, rb + g, a0, a1, b0, b1);
+      stencil_row<true, ORDERED>(G, gr, coff, ps.x, ps.y, ps.z, R, cc, kr, sh, rb + g, a0, a1, b0,
+                                 b1);
       if (a1 > a0) {
         sa = d.rstart[a0];
         la = d.rstart[a1] - sa;
@@ -968,8 +970,8 @@ __global__ __launch_bounds__(BS) void k_fpi_reaction(Dev d) {
 
 // The same with DEM_G lanes per particle, for suspensions whose fluid
 // particles couple to many spheres: a lane per slot (or candidate sphere of
-// the search), the terms passed through LDS and added in the one-lane order,
-// the same bits.  Bound by latency; the one-lane form gathers a particle's
+// the search, over pruned rows), the terms passed through LDS and added in the
+// one-lane order, the same bits.  Bound by latency; the one-lane form gathers a particle's
 // sphere records one after the other and, past RXN_CAP slots, walks the
 // rigid grid alone: slurry channel of 75,000 particles with 13.7 coupled
 // spheres each, 109 us inside the update, 29 here and 10 for the update.
@@ -1006,7 +1008,7 @@ __global__ __launch_bounds__(BS) void k_fpi_reaction_wide(Dev d) {
   } else {
     const D4 pi = d.pos[i];
     const Geo G = geo_of(B);
-    for_rigid_near(d, B, G, pi, B.couple_R + d.pad + B.act_margin, [&](int t, bool valid) {
+    for_rigid_near<true>(d, B, G, pi, B.couple_R + d.pad + B.act_margin, [&](int t, bool valid) {
       D4 v = {0.0, 0.0, 0.0, 0.0};
       if (valid) {
         const D4 f = d.rdg_c[t];

@@ -2,7 +2,9 @@
 // more cells, the partners of every particle in the order of the one-thread
 // walk and in that of several lanes per particle.  Prints one line per box:
 //   short-axis rule, particles whose order differs with pruned rows
-//   throughout, the same with the exact rows of short axes
+//   throughout, the same with the exact rows of short axes, and particles
+//   whose order differs between the whole rows and the ordered pruned ones
+//   (the reaction's walks of the rigid grid; no outer walls)
 #include <hip/hip_runtime.h>
 #undef __device__
 #define __device__ __attribute__((host)) __attribute__((device))
@@ -65,6 +67,30 @@ static int differing(const Box& b, double R) {
   return bad;
 }
 
+static int differing_ordered(const Box& b, double R) {
+  int bad = 0;
+  const int kr = reach_cells(b.G, R);
+  for (int i = 0; i < (int)b.x.size() && !b.woff; ++i) {
+    const D4 p = b.x[i];
+    int oob = 0;
+    const int cc[3] = {cell_coord(p.x, b.G, 0, &oob), cell_coord(p.y, b.G, 1, &oob),
+                       cell_coord(p.z, b.G, 2, &oob)};
+    std::vector<int> one, many;
+    for_stencil<false>(b.B, b.G, 0, p.x, p.y, p.z, R, cc, kr, [&](int c0, int c1) {
+      take(b, i, R, c0, c1, [&](int j) { one.push_back(j); });
+    });
+    const StencilShape sh = stencil_shape(b.G, cc, kr);
+    for (int r = 0; r < sh.zn * sh.yn; ++r) {
+      int a0, a1, b0, b1;
+      stencil_row<true, true>(b.B, b.G, 0, p.x, p.y, p.z, R, cc, kr, sh, r, a0, a1, b0, b1);
+      take(b, i, R, a0, a1, [&](int j) { many.push_back(j); });
+      take(b, i, R, b0, b1, [&](int j) { many.push_back(j); });
+    }
+    bad += one != many;
+  }
+  return bad;
+}
+
 int main() {
   std::mt19937_64 gen(7);
   std::uniform_real_distribution<double> u(0.0, 1.0);
@@ -111,9 +137,9 @@ int main() {
             b.item.insert(b.item.end(), c.begin(), c.end());
           }
           b.start.push_back((int)b.item.size());
-          std::printf("%d %d %d %d %d %d %d %d %d\n", kr, nx, other, per,
+          std::printf("%d %d %d %d %d %d %d %d %d %d\n", kr, nx, other, per,
                       search_axis_short(b.G, b.B.le, kr) ? 1 : 0, differing<true, false>(b, R),
                       differing<false, false>(b, R), differing<true, true>(b, R),
-                      differing<false, true>(b, R));
+                      differing<false, true>(b, R), differing_ordered(b, R));
         }
 }

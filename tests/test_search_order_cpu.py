@@ -21,9 +21,10 @@ def test_one_thread_and_several_lanes_find_partners_in_the_same_order(tmp_path):
     rows = [[int(v) for v in line.split()] for line in out.splitlines()]
     assert len(rows) == 3 * 9 * 2 * 4
     differ = 0
-    for *box, short, pruned32, pruned64, exact32, exact64 in rows:
+    for *box, short, pruned32, pruned64, exact32, exact64, ordered in rows:
         # the lanes' kernels take the exact rows in boxes of a short axis
         assert exact32 == exact64 == 0, box
+        assert ordered == 0, box
         if not short:
             assert pruned32 == pruned64 == 0, box
         differ += pruned32 + pruned64 > 0
