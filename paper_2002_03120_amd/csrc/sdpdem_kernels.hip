@@ -940,6 +940,7 @@ __device__ __forceinline__ void reaction_of(const Dev& d, const BoxD& B, int i, 
       for (int t = tb; t < te; ++t) {
         const D4 g = d.rdg_c[t];
         const double w = reaction_weight(d, G, pi, d.rpos_c[t], g.w);
+        if (w == 0.0) continue;  // out of reach, whatever its force
         a0 = __builtin_fma(-g.x, w, a0);
         a1 = __builtin_fma(-g.y, w, a1);
         a2 = __builtin_fma(-g.z, w, a2);
@@ -1012,7 +1013,8 @@ __global__ __launch_bounds__(BS) void k_fpi_reaction_wide(Dev d) {
       D4 v = {0.0, 0.0, 0.0, 0.0};
       if (valid) {
         const D4 f = d.rdg_c[t];
-        v = D4{-f.x, -f.y, -f.z, reaction_weight(d, G, pi, d.rpos_c[t], f.w)};
+        const double w = reaction_weight(d, G, pi, d.rpos_c[t], f.w);
+        if (w != 0.0) v = D4{-f.x, -f.y, -f.z, w};
       }
       wave_lds_sync();
       grp[g] = v;

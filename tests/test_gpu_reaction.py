@@ -61,3 +61,26 @@ def test_a_dense_box_keeps_its_bits_among_dilute_ones(S, L, m, shear, skin):
         g.close()
     for f, v in got[0].items():
         assert np.array_equal(v, got[1][f]), f
+
+
+@pytest.mark.parametrize("extra", [0, 4])  # several lanes per particle, one
+def test_a_sphere_out_of_reach_adds_nothing(S, extra):
+    """A sphere so fast that its drag overflows: the reaction of the fluid
+    beyond its support stays what it is without that sphere's drag."""
+    L, m = 9, 12
+    p, parts, _ = _dense(L, m, 0.0)
+    n, s = parts["id"].size, int(np.flatnonzero(parts["type"] == W.RIGID)[0])
+    parts["vel"][s] = 1e200
+    e = parts["pos"] - parts["pos"][s]
+    e -= L * np.round(e / L)
+    far = (parts["type"] == W.FLUID) & ((e * e).sum(1) > (0.25 + p["h"]) ** 2)
+    assert far.sum() > 100
+    water = W.shear_cell(12, phi=0.0, d=0.0, kBT=1e-3, shear_rate=0.0, dt=5e-4, seed=1)
+    parts, boxes, box_of = W.stack_cells([(p, parts, None)] + [water] * extra)
+    print(f"[case] {m}^3 spheres in {L}^3, one at 1e200, {extra} boxes of fluid", flush=True)
+    g = S.System(p, parts, boxes=boxes, box_of=box_of)
+    g.compute_forces(check=False)
+    f = g.read_field("F_RXN")[:n]
+    g.close()
+    assert np.isfinite(f[far]).all()
+    assert not np.isfinite(f[(parts["type"][:n] == W.FLUID) & ~far]).all()
