@@ -201,7 +201,7 @@ int sdpdem_create(const sdpdem_params* params, const sdpdem_particles* particles
  * capture, tight serving loops, harnesses that forbid hipMalloc):
  * sdpdem_create without a workspace argument.  The system lives in a
  * file-scope device array of the library, SDPDEM_STATIC_WORKSPACE_BYTES
- * (64 MiB) per device, held from the first call on a device until the
+ * (68 MiB) per device, held from the first call on a device until the
  * process ends.  The device is the current one (hipSetDevice), which must
  * be the stream's.  The call allocates no device memory (no hipMalloc,
  * hipFree or allocating library routine) and creates no stream: every
@@ -212,7 +212,7 @@ int sdpdem_create(const sdpdem_params* params, const sdpdem_particles* particles
  * device share the array: creating one overwrites the state of the
  * previous one, so use one at a time per device; calls that overlap on one
  * device race.  sdpdem_destroy releases the handle. */
-#define SDPDEM_STATIC_WORKSPACE_BYTES ((size_t)64 << 20)
+#define SDPDEM_STATIC_WORKSPACE_BYTES ((size_t)68 << 20)
 int sdpdem_create_static(const sdpdem_params* params, const sdpdem_particles* particles,
                          void* hip_stream, sdpdem_system** out);
 

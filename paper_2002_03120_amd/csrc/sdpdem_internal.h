@@ -17,7 +17,7 @@ static constexpr int BS = 256;  // threads per block of the particle kernels
 static constexpr int RXN_CAP = 16;
 // candidate rounds (64 lanes each) of a sphere's coupling search that the
 // action records for the next pass; a longer search is repeated instead
-static constexpr int ACT_ROUNDS = 15;
+static constexpr int ACT_ROUNDS = 16;
 // lanes per sphere in the contact kernels, and ints per sphere of its partner
 // list (the count and up to DEM_ROW - 1 partners)
 static constexpr int DEM_G = 16, DEM_ROW = 64;
