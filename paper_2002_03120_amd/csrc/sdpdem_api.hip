@@ -501,7 +501,20 @@ bool plan(const sdpdem_params* P, const sdpdem_box* boxes, int nbox,
     B.count = (int)r.size();
     first += (int64_t)r.size();
     B.noise = (hb.kBT > 0.0 && P->coeff_t != 0.0) ? 1 : 0;
-    B.kTf = (float)hb.kBT;
+    {
+      // sa sqrt(1/2) and sqrt(2/3 sa^2 + 1/3 sb^2), sa^2 = 4 kT C_A F / (d_i d_j)
+      // and sb^2 likewise with C_B; 2/3 C_A + 1/3 C_B = 3 xi
+      const double cn = P->coeff_t / std::sqrt(P->dt);
+      const double CA = std::max(20.0 * P->eta / 3.0 - 4.0 * P->xi, 0.0);
+      const double across = cn * std::sqrt(2.0 * hb.kBT * CA);
+      int e = 0;
+      const double m = across > 0.0 && std::isfinite(across) ? std::frexp(across, &e) : 1.0;
+      B.across = (float)(across / m);
+      B.along = (float)(cn * std::sqrt(12.0 * hb.kBT * P->xi) / m);
+      const double nl = -2.0 * std::log(2.0) * m * m;
+      B.nl_hi = (float)nl;
+      B.nl_lo = (float)(nl - (double)B.nl_hi);
+    }
     B.key0 = (uint32_t)(hb.seed & 0xffffffffu);
     B.key1 = (uint32_t)(hb.seed >> 32);
     int64_t id0 = r.empty() ? 0 : q->id[r[0]];
@@ -609,10 +622,6 @@ void fill_constants(sdpdem_system* s, const Sizes& z) {
   d.hf = (float)P.h;
   d.inv_hf = (float)(1.0 / P.h);
   d.cFf = (float)(315.0 / (4.0 * kPi * std::pow(P.h, 5)));
-  d.CAf = (float)(20.0 * P.eta / 3.0 - 4.0 * P.xi);
-  d.CBf = (float)(17.0 * P.xi - 40.0 * P.eta / 3.0);
-  d.inv_sqrt_dtf = (float)(1.0 / std::sqrt(P.dt));
-  d.cC = (float)P.coeff_c;
   d.coef_c = P.coeff_c;
   {
     double CA = 20.0 * P.eta / 3.0 - 4.0 * P.xi, CB = 17.0 * P.xi - 40.0 * P.eta / 3.0;
@@ -620,9 +629,6 @@ void fill_constants(sdpdem_system* s, const Sizes& z) {
     d.kBf = (float)(-P.coeff_d * (CA + 2.0 * CB) / 3.0);
     d.kRf = (float)(-P.coeff_r * CA * 0.5);
   }
-  d.cD = (float)P.coeff_d;
-  d.cR = (float)P.coeff_r;
-  d.cT = (float)P.coeff_t;
   d.leverf = (float)(0.5 * P.dx);
   s->noise = false;
   for (const BoxD& B : z.boxes) s->noise = s->noise || B.noise;

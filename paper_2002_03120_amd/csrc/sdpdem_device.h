@@ -736,15 +736,14 @@ __device__ __forceinline__ float sqrtf_nr(float x) {
   return x >= 1.17549435e-38f ? r : 0.0f;
 }
 
-// -2 ln(u) for u in [2^-24, 1] from the hardware log2, the product with
-// -2 ln 2 carried to twice the precision (no contraction: t must be the
-// rounded product whose error the inner operation finds).  Over every u its
-// square root below errs by at most 1.28e-7, 3.49e-8 in the mean square (the
-// library's logarithm and square root: 1.49e-7 and 3.77e-8).
-__device__ __forceinline__ float minus_2_log(float u) {
+// -2 m^2 ln(u) for u in [2^-24, 1] from the hardware log2, the product with
+// hi + lo = -2 m^2 ln 2 carried to twice the precision (no contraction: t must
+// be the rounded product whose error the inner operation finds), so that a
+// factor of the normals costs neither an operation nor a rounding.  For m = 1,
+// over every u its square root below errs by at most 1.28e-7, 3.49e-8 in the
+// mean square (the library's logarithm and square root: 1.49e-7 and 3.77e-8).
+__device__ __forceinline__ float minus_2_log(float u, float hi, float lo) {
 #pragma clang fp contract(off)
-  constexpr float hi = -1.3862943611198906f;
-  constexpr float lo = (float)(-1.3862943611198906188 - (double)hi);
   const float l = __builtin_amdgcn_logf(u);
   const float t = l * hi;
   return t + __builtin_fmaf(l, lo, __builtin_fmaf(l, hi, -t));
@@ -774,17 +773,19 @@ __device__ __forceinline__ float u01(uint32_t x) {
   return (float)((x >> 8) + 1u) * 5.9604644775390625e-8f;  // (0, 1], exact
 }
 
-// four standard normals of the unordered pair {a, b} at a step (one Philox
-// block, Box-Muller on two pairs of uniforms): three across e_ij and one
-// along it, the thermal force of Eq. FijT in its pair frame
+// four normals of the unordered pair {a, b} at a step (one Philox block,
+// Box-Muller on two pairs of uniforms), of deviation m for the factor that
+// nl_hi and nl_lo carry (minus_2_log): three across e_ij and one along it, the
+// thermal force of Eq. FijT in its pair frame
 __device__ __forceinline__ void pair_normals(uint32_t a, uint32_t b, uint32_t step, uint32_t k0,
-                                             uint32_t k1, float z[4]) {
+                                             uint32_t k1, float nl_hi, float nl_lo,
+                                             float z[4]) {
   uint32_t c0 = a < b ? a : b, c1 = a < b ? b : a, c2 = step, c3 = 0u;
   philox10(c0, c1, c2, c3, k0, k1);
   const float u[4] = {u01(c0), u01(c1), u01(c2), u01(c3)};
 #pragma unroll
   for (int m = 0; m < 2; ++m) {
-    const float rad = sqrtf_nr(minus_2_log(u[2 * m]));
+    const float rad = sqrtf_nr(minus_2_log(u[2 * m], nl_hi, nl_lo));
     // sin and cos of 2 pi u by the hardware units, whose argument is in
     // revolutions (largest error 1.3e-7 over every u this generator makes)
     const float cs = __builtin_amdgcn_cosf(u[2 * m + 1]), sn = __builtin_amdgcn_sinf(u[2 * m + 1]);

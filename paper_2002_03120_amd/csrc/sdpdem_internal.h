@@ -107,7 +107,11 @@ struct BoxD {
   // reaches act_margin farther, the flow's largest drift before a search
   double shear_reach, act_margin;
   int noise;          // thermal forces on
-  float kTf;
+  // thermal amplitudes of a pair across and along its axis over
+  // sqrt(F / (d_i d_j)), with 1 / sqrt(dt), less a common factor m in [1/2, 1)
+  // that makes the first a power of two; the normals carry m: -2 m^2 ln 2 as
+  // the sum of two floats
+  float across, along, nl_hi, nl_lo;
   uint32_t key0, key1;
   uint32_t id_base;   // smallest id in the box: noise counters use ids above it
 };
@@ -147,7 +151,7 @@ struct Dev {
   // single-precision pair constants
   float kAf, kBf, kRf;  // folded coefficients of the pair force
   double coef_c;
-  float hf, inv_hf, cFf, CAf, CBf, inv_sqrt_dtf, cC, cD, cR, cT, leverf;
+  float hf, inv_hf, cFf, leverf;
   int ncells_all, rncells_all;  // cells of all boxes
   const BoxD* boxes;
   const int2* blk;   // per launch block: (box, first sorted index); box -1 = idle

@@ -663,7 +663,7 @@ struct PairCtx {
   Geo G;
   uint32_t ib, gi;  // box's first id, box-local noise index of i
   float jump;
-  float across, along;  // thermal amplitudes over sqrt(F / (d_i d_j))
+  float across, along, nl_hi, nl_lo;  // thermal amplitudes (BoxD)
   bool le, noise;
   uint32_t key0, key1, step;
 };
@@ -678,10 +678,10 @@ __device__ __forceinline__ PairCtx pair_ctx(const Dev& d, const BoxD& B, const P
   c.le = c.G.le;
   c.jump = (float)c.G.le_jump;
   c.noise = NOISE && B.noise;
-  // sa sqrt(1/2) and sqrt(2/3 sa^2 + 1/3 sb^2), sa^2 = 4 kT C_A F / (d_i d_j)
-  const float cn = d.cT * d.inv_sqrt_dtf, kT4 = 4.0f * B.kTf;
-  c.across = NOISE ? cn * sqrtf(0.5f * kT4 * d.CAf) : 0.0f;
-  c.along = NOISE ? cn * sqrtf(kT4 * (d.CAf * (2.0f / 3.0f) + d.CBf * (1.0f / 3.0f))) : 0.0f;
+  c.across = NOISE ? B.across : 0.0f;
+  c.along = NOISE ? B.along : 0.0f;
+  c.nl_hi = NOISE ? B.nl_hi : 0.0f;
+  c.nl_lo = NOISE ? B.nl_lo : 0.0f;
   c.key0 = B.key0;
   c.key1 = B.key1;
   c.step = NOISE ? (uint32_t)d.dstep[0] : 0u;  // noise counter
@@ -743,7 +743,7 @@ __device__ __forceinline__ void pair_terms(const Dev& d, const PairCtx& c, const
     // z2) plus z3 along e, s_ij = +1 for gid_i < gid_j (F_ji = -F_ij)
     float z[4];
     const uint32_t gi = c.gi, gj = (uint32_t)rj.gid - c.ib;
-    pair_normals(gi, gj, c.step, c.key0, c.key1, z);
+    pair_normals(gi, gj, c.step, c.key0, c.key1, c.nl_hi, c.nl_lo, z);
     const float ze = fma(z[2], ez, fma(z[0], ex, z[1] * ey));
     const float px = fma(-ze, ex, z[0]), py = fma(-ze, ey, z[1]), pz = fma(-ze, ez, z[2]);
     const float sf = sqrtf_nr(fdd);
