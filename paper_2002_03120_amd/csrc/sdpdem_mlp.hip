@@ -62,8 +62,12 @@ __device__ __forceinline__ float silu_grad(float z) {
 // sum of three bfloat16 parts (its top 8 significant bits, the next 8, the
 // last 8), so three bf16 products accumulated in FP32 give the FP32
 // product, and the layer equals its FP32 evaluation up to the order of the
-// sums.  A block stages the hidden layers' weights in LDS once and its
-// wavefronts then take groups of 16 rows in turn.
+// sums.  The last parts are added first, over both chunks of the contraction,
+// then the middle ones: only the two products of the leading parts round at
+// the size of the whole sum (error over 2^12 rows, 2-norm, by chunk and by
+// part: 2.55e-7 and 1.95e-7, the time alike).  A block stages the hidden
+// layers' weights in LDS once and its wavefronts then take groups of 16 rows
+// in turn.
 
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef unsigned short v8u16 __attribute__((ext_vector_type(8)));
@@ -159,16 +163,18 @@ __global__ __launch_bounds__(64 * PRED_WAVES) void k_mlp_predict(
 #pragma unroll
       for (int jt = 0; jt < 4; ++jt) {
         v4f acc = *reinterpret_cast<const v4f*>(&bias[l + 1][16 * jt + 4 * q]);
+        v8bf wv[2];
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const v8bf wv = __builtin_bit_cast(
+        for (int c = 0; c < 2; ++c)
+          wv[c] = __builtin_bit_cast(
               v8bf, *reinterpret_cast<const v8u16*>(wt + (((l * 4 + jt) * 2 + c) * 64 + lane) * 8));
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv, __builtin_bit_cast(v8bf, ah[c]), acc,
-                                                        0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv, __builtin_bit_cast(v8bf, am[c]), acc,
-                                                        0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv, __builtin_bit_cast(v8bf, al[c]), acc,
-                                                        0, 0, 0);
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+#pragma unroll
+          for (int c = 0; c < 2; ++c)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                wv[c], __builtin_bit_cast(v8bf, m == 0 ? al[c] : m == 1 ? am[c] : ah[c]), acc, 0, 0,
+                0);
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) h[jt][v] = silu(acc[v]);
