@@ -208,7 +208,7 @@ struct Train {
   uint16_t* wpk;  // hidden weights again, in the order of packed_index
   float* loss;
   float* part;   // [GROUPS][NP]: every group's share of the gradient
-  float* lpart;  // [GROUPS]: its sum of squared residuals
+  double* lpart;  // [GROUPS]: its sum of squared residuals
 };
 
 // acc += A[16 x K] B[K x 16] on the FP32 matrix cores.  Lane (r = lane % 16,
@@ -237,7 +237,8 @@ __global__ __launch_bounds__(256) void k_mlp_grad(Train T, Norm nrm, const float
                                                   const float* __restrict__ t, int B) {
   __shared__ __attribute__((aligned(16))) uint16_t ws[2][HID * LDW];  // W2, W3
   __shared__ float xn[16 * 4], act[3][16 * LDA], slope[3][16 * LDA], dzb[2][16 * LDA];
-  __shared__ float dy[16], sq[16], w4[HID];
+  __shared__ float dy[16], w4[HID];
+  __shared__ double sq[16];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r = lane & 15, q = lane >> 4;
   const int row0 = 16 * (int)blockIdx.x;
   float* const part = T.part + (size_t)blockIdx.x * NP;
@@ -285,7 +286,7 @@ __global__ __launch_bounds__(256) void k_mlp_grad(Train T, Norm nrm, const float
     if (c == 0) {
       const float res = row0 + i < B ? y + bf16_to_f32(T.wq[OB4]) - t[row0 + i] : 0.0f;
       dy[i] = 2.0f * res / (float)B;
-      sq[i] = res * res;
+      sq[i] = (double)res * res;
     }
   }
   __syncthreads();
@@ -296,7 +297,8 @@ __global__ __launch_bounds__(256) void k_mlp_grad(Train T, Norm nrm, const float
     for (int i = 0; i < 16; ++i) s += act[2][i * LDA + tid] * dy[i];
     part[OW4 + tid] = s;
   } else if (tid == HID) {
-    float s = 0.0f, l2 = 0.0f;
+    float s = 0.0f;
+    double l2 = 0.0;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       s += dy[i];
@@ -369,9 +371,9 @@ __global__ __launch_bounds__(256) void k_mlp_update(Train T, int B, int update, 
   const int p = blockIdx.x * 256 + threadIdx.x;
   const int ng = (B + 15) / 16;
   if (p == 0) {
-    float s = 0.0f;
+    double s = 0.0;
     for (int k = 0; k < ng; ++k) s += T.lpart[k];
-    T.loss[0] = s / (float)B;
+    T.loss[0] = (float)(s / (double)B);
   }
   if (p >= NP) return;
   float pk[GROUPS];
@@ -424,7 +426,7 @@ size_t mlp_layout(char* base, Train* T) {
   t.m = b.take<float>(NP);
   t.v = b.take<float>(NP);
   t.part = b.take<float>((size_t)GROUPS * NP);
-  t.lpart = b.take<float>(GROUPS);
+  t.lpart = b.take<double>(GROUPS);
   if (T) *T = t;
   return b.off + 256;
 }

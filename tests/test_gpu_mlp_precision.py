@@ -38,3 +38,20 @@ def test_error_of_the_inference(mlp):
     rms = float(np.sqrt(np.mean(np.square(off))))
     print(f"[case] 16 networks, 4096 rows: {rms:.3g}", flush=True)
     assert rms < 2.3e-7
+
+
+def test_error_of_the_loss(mlp):
+    """One rounding to 32 bits, below 2^-24 (2.5e-8 in the mean square with the
+    mantissas spread evenly), and the residuals' own, which average out over
+    the rows: 4e-8 at most."""
+    off = []
+    for seed in range(100, 164):
+        p, x = W.mlp_init(seed), W.mlp_queries(256, seed)
+        t = (2.5 * x[:, 0] + 4.0 * x[:, 0] ** 2).astype(np.float32)
+        net = mlp.Mlp(p, NORM)
+        net.train_step(_dev(x), _dev(t), update=False)
+        ref, _ = M.loss_and_grad(p, x, t, NORM)
+        off.append(net.read()[3] / ref - 1.0)
+    rms = float(np.sqrt(np.mean(np.square(off))))
+    print(f"[case] 64 networks, 256 rows: {rms:.3g}", flush=True)
+    assert rms < 4e-8
