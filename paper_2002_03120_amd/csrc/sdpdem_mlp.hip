@@ -12,8 +12,8 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <memory>
 #include <new>
-#include <vector>
 
 #include "sdpdem.h"
 #include "sdpdem_mlp.h"
@@ -526,35 +526,41 @@ int sdpdem_mlp_read(sdpdem_mlp* m, float* params, float* used_params, float* gra
   // One copy of everything between the first and the last array asked for:
   // four copies took 60 us where the training step itself takes 15; one
   // takes 27 (25 into pinned memory, which costs a new network 90 us).
+  // Without memory for it every array is copied by itself.
   char* const base = reinterpret_cast<char*>(m->T.master);
   const struct {
     const void* dev;
     size_t bytes;
-    bool want;
-  } part[4] = {{m->T.master, sizeof(float) * NP, params != nullptr},
-               {m->T.grad, sizeof(float) * NP, grad != nullptr},
-               {m->T.loss, sizeof(float), loss != nullptr},
-               {m->T.wq, sizeof(uint16_t) * NP, used_params != nullptr}};
+    void* out;
+  } part[4] = {{m->T.master, sizeof(float) * NP, params},
+               {m->T.grad, sizeof(float) * NP, grad},
+               {m->T.loss, sizeof(float), loss},
+               // the upper half of the array, widened in place below
+               {m->T.wq, sizeof(uint16_t) * NP,
+                used_params ? reinterpret_cast<uint16_t*>(used_params) + NP : nullptr}};
   size_t off[4], lo = SIZE_MAX, hi = 0;
   for (int k = 0; k < 4; ++k) {
     off[k] = (size_t)(static_cast<const char*>(part[k].dev) - base);
-    if (!part[k].want) continue;
+    if (!part[k].out) continue;
     lo = std::min(lo, off[k]);
     hi = std::max(hi, off[k] + part[k].bytes);
   }
-  std::vector<char> host(off[3] + part[3].bytes);
-  char* const to = host.data();
-  if (lo < hi && hipMemcpyAsync(to + lo, base + lo, hi - lo, hipMemcpyDeviceToHost, st) !=
-                     hipSuccess)
-    return SDPDEM_E_HIP;
-  if (hipStreamSynchronize(st) != hipSuccess) return SDPDEM_E_HIP;
-  if (params) std::memcpy(params, to + off[0], part[0].bytes);
-  if (grad) std::memcpy(grad, to + off[1], part[1].bytes);
-  if (loss) std::memcpy(loss, to + off[2], part[2].bytes);
+  const std::unique_ptr<char[]> host(lo < hi ? new (std::nothrow) char[hi - lo] : nullptr);
+  bool ok = !host || hipMemcpyAsync(host.get(), base + lo, hi - lo, hipMemcpyDeviceToHost, st) ==
+                         hipSuccess;
+  for (int k = 0; k < 4 && !host; ++k)
+    ok = ok && (!part[k].out || hipMemcpyAsync(part[k].out, part[k].dev, part[k].bytes,
+                                               hipMemcpyDeviceToHost, st) == hipSuccess);
+  ok = hipStreamSynchronize(st) == hipSuccess && ok;
+  if (!ok) return SDPDEM_E_HIP;
+  for (int k = 0; k < 4 && host; ++k)
+    if (part[k].out) std::memcpy(part[k].out, host.get() + (off[k] - lo), part[k].bytes);
   if (used_params) {
-    const uint16_t* const q = reinterpret_cast<const uint16_t*>(to + off[3]);
+    const char* const q = static_cast<const char*>(part[3].out);
     for (int p = 0; p < NP; ++p) {
-      const uint32_t u = (uint32_t)q[p] << 16;
+      uint16_t b;
+      std::memcpy(&b, q + sizeof(b) * p, sizeof(b));
+      const uint32_t u = (uint32_t)b << 16;
       std::memcpy(&used_params[p], &u, sizeof(float));
     }
   }
