@@ -351,7 +351,12 @@ int sdpdem_info(sdpdem_system* sys, int64_t out[16], void* hip_stream);
  * routines of Algs. 1 and 2.
  * Time every launch of one kernel (enum sdpdem_kernel) with HIP events on
  * the launch stream; SDPDEM_K_NONE switches timing off.  sdpdem_kernel_time
- * returns the accumulated milliseconds and launch count and resets them. */
+ * returns the accumulated milliseconds and launch count and resets them.
+ * The results are the same bits, but the launches are not quite those of an
+ * untimed step: no graph is replayed, and in a step whose first pass updates
+ * its particles in the pair kernel (no active spheres, no stress samples) a
+ * timed SDPDEM_K_FLUID_FORCES launch leaves the update to a launch of its
+ * own, as does every first pass while SDPDEM_K_INTEGRATE is timed. */
 int sdpdem_set_profiling(sdpdem_system* sys, int kernel);
 int sdpdem_kernel_time(sdpdem_system* sys, double* total_ms, int64_t* launches);
 /* Sampled per-routine timing for the breakdown of Fig. CompTimeTotal.

@@ -693,6 +693,7 @@ struct Prof {
     }
     on = ext || hipEventRecord(s->ev[s->ev_used].first, st) == hipSuccess;
   }
+  bool timed() const { return on; }
   hipEvent_t t0() const { return on && ext ? s->ev[s->ev_used].first : nullptr; }
   hipEvent_t t1() const { return on && ext ? s->ev[s->ev_used].second : nullptr; }
   ~Prof() {
@@ -838,10 +839,11 @@ bool needs_fill(const sdpdem_system* s, bool build) {
 
 // Whether the pair kernel of a step's first pass updates its particles, too:
 // without active spheres nothing else comes between, and these kernels gain by
-// it; not while a kernel is being timed, so that the figures stay those of
-// the separate kernels.
+// it.  A timed pair kernel does not (and run_pass asks only for one that is
+// not), nor any while the updates are timed, so that the figures stay those of
+// the separate kernels; the launches between timed ones stay as they are.
 bool pairs_update(const sdpdem_system* s) {
-  return !rigid_active(s) && !s->stress && s->prof_kernel == SDPDEM_K_NONE &&
+  return !rigid_active(s) && !s->stress && s->prof_kernel != SDPDEM_K_INTEGRATE &&
          forces_can_update(s->d, s->noise);
 }
 
@@ -866,9 +868,10 @@ void run_pass(sdpdem_system* s, int velver, int commit, bool integrate, bool fil
   s->rigid_issued = false;
   // a captured graph never reads the moved flag: no need to raise it
   const bool track = d.reuse && !s->capturing;
-  const bool updated = integrate && velver == 1 && pairs_update(s);
+  bool updated = false;
   {
     Prof pr(s, SDPDEM_K_FLUID_FORCES, st, true);
+    updated = integrate && velver == 1 && !pr.timed() && pairs_update(s);
     launch_fluid_forces(d, s->noise, updated, track, st, pr.t0(), pr.t1());
   }
   if (issue) {
