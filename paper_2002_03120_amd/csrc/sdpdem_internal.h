@@ -227,8 +227,8 @@ struct Dev {
   // action of the first pass after a neighbour build, cleared before it):
   int* rxn_cnt;    // spheres whose support holds the particle (0: uncoupled)
   int2* rxn_slot;  // [RXN_CAP][npad]: (cell-ordered sphere record, FP32 Lucy polynomial)
-  // per cell-ordered sphere record: the fluid particle of every lane and
-  // round of its search (-1: none), and (rounds or -1, rigid centres in H_s)
+  // per rigid slot: the partner of every lane and round of its coupling search
+  // (-1: none), and (rounds or -1, rigid centres in H_s)
   int* act_list;  // [nr][ACT_ROUNDS * 64]
   int2* act_meta;
   int* dem_list;  // [nr][DEM_ROW] by cell-ordered record: count (-1: too many), partner records

@@ -494,8 +494,9 @@ __device__ __forceinline__ int wave_sum_i(int v) {
   return v;
 }
 
-// The record of a sphere (keyed by its rigid slot, so that it survives the
-// rigid grid's re-sort every step): per round and lane the partner a
+// The record of a sphere (keyed by its rigid slot, whatever the order of the
+// rigid grid, which is re-sorted at a search and holds each sphere where the
+// search saw it until the next): per round and lane the partner a
 // search visited within H_s + skin, fluid j as j, rigid k as -2 - k, none as
 // -1.  Passes at the same sorted order read it instead of searching: the
 // same partners in the same lanes and rounds, each tested against H_s
@@ -875,6 +876,7 @@ __device__ __forceinline__ void by_box(const Dev& d, int box, Fn&& body) {
 // (a7) reaction on the coupled fluid particles, Eq. F_fpi_DG_reac
 // normalised per rigid particle: -sum_s F^DG_s w_sj / Omega_s over the
 // rigid s with j in C_s.  The rigid grid's cells are at least H_max wide.
+
 // Lucy weight of support H_s without its normalisation (folded into the
 // sphere's record; inv_H is 0 where the sphere couples to nothing): 0 outside
 __device__ __forceinline__ double reaction_weight(const Dev& d, const Geo& G, const D4& pi,
@@ -1448,14 +1450,12 @@ void launch_integrate(const Dev& d, int velver, int rigid_active, bool end_step,
 // Per-box pressure tensor component P_zx after a step: kinetic part
 // m v'_z v'_x with v' the velocity less the shear profile, plus the virial of
 // the last force evaluation (pair kernel plane 12 for fluid and inner walls,
-// wzx_r for rigid particles), over the box volume.  One block per box sums
-// its fixed particle range in a fixed order, so the result is repeatable.
-
-// Per-box pressure tensor sample in two launches with a fixed summation
-// order: each launch block sums m v_z v'_x + the virial over its particles
-// (a tree in shared memory), then one thread per box adds its blocks'
-// partial sums in block order.  A box's blocks start at its first particle,
-// so a box gives the same bits alone or in a batch.
+// wzx_r for rigid particles), over the box volume: two launches with a fixed
+// summation order.  Each launch block sums m v_z v'_x + the virial over its
+// particles (a tree in shared memory), then a workgroup per box reads its
+// blocks' partial sums and one of its threads adds them in block order.  A
+// box's blocks start at its first particle, so a box gives the same bits alone
+// or in a batch.
 __global__ __launch_bounds__(BS) void k_box_stress_part(Dev d, int rigid_active) {
   __shared__ double sh[BS];
   const unsigned lb = logical_block(d, blockIdx.x);
