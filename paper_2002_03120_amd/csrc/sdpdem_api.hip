@@ -303,8 +303,8 @@ size_t layout(const Sizes& z, char* base, sdpdem_system* s) {
   D4* rdg_c = b.take<D4>(nr);
   int* rxn_cnt = b.take<int>(nr ? np : 1);
   int2* rxn_slot = b.take<int2>(nr ? (size_t)RXN_CAP * np : 1);
-  int* act_list = b.take<int>(nr ? nr * ACT_ROUNDS * 64 : 1);
-  int* dem_list = b.take<int>(nr ? nr * DEM_ROW : 1);
+  int* act_list = b.take<int>(nr ? nr * ACT_ROW : 1);
+  int* dem_list = act_list + ACT_ROUNDS * 64;
   int2* act_meta = b.take<int2>(nr ? nr : 1);
   double* act_sum = b.take<double>(nr ? 8 * (size_t)nr : 1);
   int64_t* dstep = b.take<int64_t>(1);

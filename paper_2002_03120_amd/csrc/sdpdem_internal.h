@@ -21,6 +21,10 @@ static constexpr int ACT_ROUNDS = 16;
 // lanes per sphere in the contact kernels, and ints per sphere of its partner
 // list (the count and up to DEM_ROW - 1 partners)
 static constexpr int DEM_G = 16, DEM_ROW = 64;
+// ints from one sphere's record to the next: the partner lists lie between
+// the records, whose rows 4 KiB apart would share too few memory channels
+// (dam break with 20,000 spheres, action 81.3 and 80.5 us)
+static constexpr int ACT_ROW = ACT_ROUNDS * 64 + DEM_ROW;
 
 enum : uint8_t { T_FLUID = 0, T_RIGID = 1, T_INNER = 2, T_OUTER = 3 };
 
@@ -151,7 +155,7 @@ struct Dev {
   // single-precision pair constants
   float kAf, kBf, kRf;  // folded coefficients of the pair force
   double coef_c;
-  float hf, inv_hf, cFf, leverf;
+  float hf, inv_hf, cFf;
   int ncells_all, rncells_all;  // cells of all boxes
   const BoxD* boxes;
   const int2* blk;   // per launch block: (box, first sorted index); box -1 = idle
@@ -161,6 +165,9 @@ struct Dev {
   int nablk, ablk_per;
   int nactive;       // particles of the boxes' active parts
   int act_wide;      // a workgroup instead of a wave per sphere in the coupling action
+  // half the particle distance; away from the constants the pair loop starts
+  // with: loaded with them it delays the kernel's first loads (0.5 % of it)
+  float leverf;
   const int* rbox;   // box of every rigid slot
   // particles (current buffer)
   D4* pos;  // x, y, z, radius (lever for fluid and walls)
@@ -229,9 +236,11 @@ struct Dev {
   int2* rxn_slot;  // [RXN_CAP][npad]: (cell-ordered sphere record, FP32 Lucy polynomial)
   // per rigid slot: the partner of every lane and round of its coupling search
   // (-1: none), and (rounds or -1, rigid centres in H_s)
-  int* act_list;  // [nr][ACT_ROUNDS * 64]
+  int* act_list;  // [nr][ACT_ROW], the first ACT_ROUNDS * 64 of each
   int2* act_meta;
-  int* dem_list;  // [nr][DEM_ROW] by cell-ordered record: count (-1: too many), partner records
+  // [nr][ACT_ROW], the first DEM_ROW of each, by cell-ordered record: count
+  // (-1: too many), partner records
+  int* dem_list;
   // per cell-ordered sphere record: the action's sums Omega_s, sum w v (3),
   // sum w (F^C + F^D) (3) and the lever sum w r_z, for the finishing kernel
   double* act_sum;  // [nr][8]

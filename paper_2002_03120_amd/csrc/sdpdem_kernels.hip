@@ -544,7 +544,7 @@ __global__ __launch_bounds__(W == 1 ? BS : 64 * W) __attribute__((amdgpu_waves_p
   const double R = ps.w, H = R + d.h, H2 = H * H;
   const double invH = 1.0 / H, wnorm = 105.0 / (16.0 * PI * H * H * H);  // Eq. kernel
   const size_t np = (size_t)d.npad;
-  int* const list = d.act_list + (size_t)s * (ACT_ROUNDS * 64);
+  int* const list = d.act_list + (size_t)s * ACT_ROW;
   // W = 1: the lane's sums; else lane l of wave c holds component c of lane l
   double acc[W == 1 ? NC : 1];
 #pragma unroll
@@ -1167,7 +1167,7 @@ __global__ __launch_bounds__(BS) void k_dem_find(Dev d) {
     // partners come within R_s + R_k + h before the next search if they are
     // within 2 skin more of it now (pad: skin / 2)
     const double reach = ps.w + d.h + 4.0 * d.pad * (1.0 + 1e-9);
-    int* const list = d.dem_list + (size_t)me * DEM_ROW;
+    int* const list = d.dem_list + (size_t)me * ACT_ROW;
     int cnt = 0;
     for_rigid_near(d, B, G, ps, reach + (B.couple_R - d.h), [&](int t, bool valid) {
       bool in = false;
@@ -1218,7 +1218,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_
         ncnt += __popc(m);
       }
     };
-    const int* const list = d.dem_list + (size_t)me * DEM_ROW;
+    const int* const list = d.dem_list + (size_t)me * ACT_ROW;
     const int cnt = list[0];
     if (cnt >= 0) {
       for (int k = g; k - g < cnt; k += DEM_G) round(k < cnt ? list[1 + k] : me, k < cnt);
