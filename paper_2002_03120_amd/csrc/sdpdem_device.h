@@ -239,12 +239,13 @@ __device__ __forceinline__ double slab_dist(double x, double lo, double cs) {
 // the row at unwrapped z and y cell indices (zu, yu); every operation rounded
 // (no contraction), so that the same row comes out in every kernel.  ORDERED:
 // the cells of a pruned row in the order the whole row has them, which starts
-// at cell 0 where it takes the x axis whole.
+// at cell 0 where it takes the x axis whole (*all then).
 template <bool PRUNE, bool ORDERED = false>
 __device__ __forceinline__ void stencil_row_zy(const Geo& B, const Grid& G, int off, double px,
                                                double py, double pz, double R, const int cc[3],
                                                int k, const StencilShape& sh, int zu, int yu,
-                                               int& a0, int& a1, int& b0, int& b1) {
+                                               int& a0, int& a1, int& b0, int& b1,
+                                               bool* all = nullptr) {
 #pragma clang fp contract(off)
   a0 = a1 = b0 = b1 = 0;
   const int nx = G.nc[0], ny = G.nc[1], nz = G.nc[2];
@@ -324,6 +325,7 @@ __device__ __forceinline__ void stencil_row_zy(const Geo& B, const Grid& G, int 
     }
   }
   const int rowkey = off + (z * ny + y) * nx;
+  if (ORDERED && all) *all = G.per[0] && whole;
   if (G.per[0] && xn >= nx) {
     a0 = rowkey;
     a1 = rowkey + nx;
@@ -380,18 +382,91 @@ __device__ __forceinline__ void for_stencil(const Geo& B, const Grid& G, int off
     }
 }
 
-// The rows of a pruned stencil in single precision, on coordinates relative
-// to the point's own cell (so their magnitude stays below a few cells).  Every
-// bound carries a relative margin of 1e-5 of a cell, far above the FP32
-// rounding of these small numbers, so the runs may hold a few extra cells but
-// never miss one; the distance test in FP64 decides.  Sheared boxes (measured:
-// the generic rows are faster there), stencils that wrap onto themselves and
-// points outside their cell take the generic rows.  The walks of one and of
-// several lanes per particle share these functions, and no operation in them
-// is contracted: both take the same runs in the same order.
+// The rows of for_stencil<true> for one thread, with the row geometry in
+// single precision on coordinates relative to the point's own cell (so
+// their magnitude stays below a few cells): the z distance is formed once
+// per z row, rows are walked z-major without an integer division, and the
+// x reach takes one FP32 square root.  Every bound carries a relative
+// margin of 1e-5 of a cell, far above the FP32 rounding of these small
+// numbers, so the runs may hold a few extra cells but never miss one; the
+// distance test in FP64 decides.  Sheared boxes (measured: the generic
+// rows are faster there), stencils that wrap onto themselves and points
+// outside their cell take the generic rows.
+template <class Fn>
+__device__ __forceinline__ void for_stencil_pruned(const Geo& B, const Grid& G, int off, double px,
+                                                   double py, double pz, double R,
+                                                   const int cc[3], int k, Fn&& fn) {
+#pragma clang fp contract(off)
+  const double fxd = px - (G.lo[0] + (double)cc[0] * G.cs[0]);
+  const double fyd = py - (G.lo[1] + (double)cc[1] * G.cs[1]);
+  const double fzd = pz - (G.lo[2] + (double)cc[2] * G.cs[2]);
+  const int nx = G.nc[0], ny = G.nc[1], nz = G.nc[2];
+  const bool plain = !B.le && !(G.per[2] && 2 * k + 1 > nz) && !(G.per[1] && 2 * k + 1 > ny) &&
+                     fxd > -G.cs[0] && fxd < 2.0 * G.cs[0] && fyd > -G.cs[1] &&
+                     fyd < 2.0 * G.cs[1] && fzd > -G.cs[2] && fzd < 2.0 * G.cs[2];
+  if (!plain) {
+    for_stencil<true>(B, G, off, px, py, pz, R, cc, k, fn);
+    return;
+  }
+  const float fx = (float)fxd, fy = (float)fyd, fz = (float)fzd;
+  const float csx = (float)G.cs[0], csy = (float)G.cs[1], csz = (float)G.cs[2];
+  const float icx = (float)G.inv_cs[0];
+  const float R2 = (float)(R * R) * (1.0f + 1e-5f);
+  const float mx = 1e-5f * csx;
+  for (int dz = -k; dz <= k; ++dz) {
+    int z = cc[2] + dz;
+    if (z < 0 || z >= nz) {
+      if (!G.per[2]) continue;
+      z += z < 0 ? nz : -nz;
+    }
+    const float sz = fmaxf(0.0f, fmaxf((float)dz * csz - fz, fz - (float)(dz + 1) * csz));
+    const float z2 = sz * sz;
+    if (z2 >= R2) continue;
+    for (int dy = -k; dy <= k; ++dy) {
+      int y = cc[1] + dy;
+      if (y < 0 || y >= ny) {
+        if (!G.per[1]) continue;
+        y += y < 0 ? ny : -ny;
+      }
+      const float sy = fmaxf(0.0f, fmaxf((float)dy * csy - fy, fy - (float)(dy + 1) * csy));
+      const float d2 = z2 + sy * sy;
+      if (d2 >= R2) continue;
+      const float rx = __builtin_amdgcn_sqrtf(R2 - d2) * (1.0f + 1e-5f) + mx;
+      const int xa = max(cc[0] + (int)floorf((fx - rx) * icx), cc[0] - k);
+      const int xb = min(cc[0] + (int)floorf((fx + rx) * icx), cc[0] + k);
+      if (xb < xa) continue;
+      const int rowkey = off + (z * ny + y) * nx;
+      if (!G.per[0]) {
+        const int lo = max(xa, 0), hi = min(xb, nx - 1);
+        if (lo <= hi) fn(rowkey + lo, rowkey + hi + 1);
+      } else if (xb - xa + 1 >= nx) {
+        fn(rowkey, rowkey + nx);
+      } else {
+        // xa (within k cells of the row) into [0, nx) without a division
+        const int lo = xa < 0 ? xa + nx : (xa >= nx ? xa - nx : xa);
+        const int hi = lo + (xb - xa);  // at most one wrap
+        if (hi >= nx) {
+          fn(rowkey + lo, rowkey + nx);
+          fn(rowkey, rowkey + hi - nx + 1);
+        } else {
+          fn(rowkey + lo, rowkey + hi + 1);
+        }
+      }
+    }
+  }
+}
+
+// One row of for_stencil_pruned: z and y cells cc + dz, cc + dy of a point at
+// f (single precision, relative to its own cell), as stencil_row gives it.
+// The same margins hold: extra cells, never a missing one.  The same operations
+// in both, none contracted: the same runs in the same order.  (Two texts, since
+// the one-thread search loses by a common one: over these runs, 1,000,000
+// particles in cells of h 305 us in place of 287 and in sheared boxes 315 in
+// place of 291, though 242 in place of 260 in cells of 0.55 h; with the parts
+// of a row in functions 286 there, too.)
 struct PlainRows {
   float fx, fy, fz, csx, csy, csz, icx, R2;
-  bool plain;
+  bool plain;  // the conditions for_stencil_pruned names
 };
 
 __device__ __forceinline__ PlainRows plain_rows(const Geo& B, const Grid& G, double px, double py,
@@ -415,33 +490,30 @@ __device__ __forceinline__ PlainRows plain_rows(const Geo& B, const Grid& G, dou
   return p;
 }
 
-// squared distance of f to the slab of cells dc from its own
-__device__ __forceinline__ float plain_gap2(float f, float cs, int dc) {
+__device__ __forceinline__ void plain_row(const PlainRows& p, const Grid& G, int off,
+                                          const int cc[3], int k, int dz, int dy, int& a0, int& a1,
+                                          int& b0, int& b1) {
 #pragma clang fp contract(off)
-  const float s = fmaxf(0.0f, fmaxf((float)dc * cs - f, f - (float)(dc + 1) * cs));
-  return s * s;
-}
-
-// cell c of an axis of n, wrapped; false past a wall
-__device__ __forceinline__ bool plain_cell(int& c, int n, int per) {
-  if (c < 0 || c >= n) {
-    if (!per) return false;
-    c += c < 0 ? n : -n;
-  }
-  return true;
-}
-
-// the runs of the row whose slab lies d2 (squared, below R2) from the point
-__device__ __forceinline__ void plain_runs(const PlainRows& p, const Grid& G, int rowkey,
-                                           const int cc[3], int k, float d2, int& a0, int& a1,
-                                           int& b0, int& b1) {
-#pragma clang fp contract(off)
-  const int nx = G.nc[0];
   a0 = a1 = b0 = b1 = 0;
+  const int nx = G.nc[0], ny = G.nc[1], nz = G.nc[2];
+  int z = cc[2] + dz, y = cc[1] + dy;
+  if (z < 0 || z >= nz) {
+    if (!G.per[2]) return;
+    z += z < 0 ? nz : -nz;
+  }
+  if (y < 0 || y >= ny) {
+    if (!G.per[1]) return;
+    y += y < 0 ? ny : -ny;
+  }
+  const float sz = fmaxf(0.0f, fmaxf((float)dz * p.csz - p.fz, p.fz - (float)(dz + 1) * p.csz));
+  const float sy = fmaxf(0.0f, fmaxf((float)dy * p.csy - p.fy, p.fy - (float)(dy + 1) * p.csy));
+  const float d2 = sz * sz + sy * sy;
+  if (d2 >= p.R2) return;
   const float rx = __builtin_amdgcn_sqrtf(p.R2 - d2) * (1.0f + 1e-5f) + 1e-5f * p.csx;
   const int xa = max(cc[0] + (int)floorf((p.fx - rx) * p.icx), cc[0] - k);
   const int xb = min(cc[0] + (int)floorf((p.fx + rx) * p.icx), cc[0] + k);
   if (xb < xa) return;
+  const int rowkey = off + (z * ny + y) * nx;
   if (!G.per[0]) {
     const int lo = max(xa, 0), hi = min(xb, nx - 1);
     if (lo <= hi) {
@@ -452,7 +524,6 @@ __device__ __forceinline__ void plain_runs(const PlainRows& p, const Grid& G, in
     a0 = rowkey;
     a1 = rowkey + nx;
   } else {
-    // xa (within k cells of the row) into [0, nx) without a division
     const int lo = xa < 0 ? xa + nx : (xa >= nx ? xa - nx : xa);
     const int hi = lo + (xb - xa);  // at most one wrap
     a0 = rowkey + lo;
@@ -460,50 +531,6 @@ __device__ __forceinline__ void plain_runs(const PlainRows& p, const Grid& G, in
     if (hi >= nx) {
       b0 = rowkey;
       b1 = rowkey + hi - nx + 1;
-    }
-  }
-}
-
-// the row of z and y cells cc + dz, cc + dy
-__device__ __forceinline__ void plain_row(const PlainRows& p, const Grid& G, int off,
-                                          const int cc[3], int k, int dz, int dy, int& a0, int& a1,
-                                          int& b0, int& b1) {
-#pragma clang fp contract(off)
-  a0 = a1 = b0 = b1 = 0;
-  int z = cc[2] + dz, y = cc[1] + dy;
-  if (!plain_cell(z, G.nc[2], G.per[2]) || !plain_cell(y, G.nc[1], G.per[1])) return;
-  const float d2 = plain_gap2(p.fz, p.csz, dz) + plain_gap2(p.fy, p.csy, dy);
-  if (d2 >= p.R2) return;
-  plain_runs(p, G, off + (z * G.nc[1] + y) * G.nc[0], cc, k, d2, a0, a1, b0, b1);
-}
-
-// The rows of for_stencil<true> for one thread: where they are plain, the z
-// distance is formed once per z row and rows are walked z-major without an
-// integer division.
-template <class Fn>
-__device__ __forceinline__ void for_stencil_pruned(const Geo& B, const Grid& G, int off, double px,
-                                                   double py, double pz, double R,
-                                                   const int cc[3], int k, Fn&& fn) {
-#pragma clang fp contract(off)
-  const PlainRows p = plain_rows(B, G, px, py, pz, R, cc, k);
-  if (!p.plain) {
-    for_stencil<true>(B, G, off, px, py, pz, R, cc, k, fn);
-    return;
-  }
-  for (int dz = -k; dz <= k; ++dz) {
-    int z = cc[2] + dz;
-    if (!plain_cell(z, G.nc[2], G.per[2])) continue;
-    const float z2 = plain_gap2(p.fz, p.csz, dz);
-    if (z2 >= p.R2) continue;
-    for (int dy = -k; dy <= k; ++dy) {
-      int y = cc[1] + dy;
-      if (!plain_cell(y, G.nc[1], G.per[1])) continue;
-      const float d2 = z2 + plain_gap2(p.fy, p.csy, dy);
-      if (d2 >= p.R2) continue;
-      int a0, a1, b0, b1;
-      plain_runs(p, G, off + (z * G.nc[1] + y) * G.nc[0], cc, k, d2, a0, a1, b0, b1);
-      if (a1 > a0) fn(a0, a1);
-      if (b1 > b0) fn(b0, b1);
     }
   }
 }
@@ -526,23 +553,39 @@ __device__ __forceinline__ void for_search(const Geo& B, const Grid& G, int off,
 // With cells of R or more the rows are pruned, too, and in the candidate search
 // they are the generic ones throughout (FP32 false: no registers to spare, 43
 // -> 50 us on 83,000 particles).  A pruned row starts at its own first cell
-// and wraps, one that takes the x axis whole starts at cell 0: where a row can
-// do that in either walk (EXACT and a short axis, search_axis_short) the row is
-// exactly the one-thread walk's.
+// and wraps, one that takes the x axis whole starts at cell 0.  Where a row can
+// do that in either walk (EXACT and a short axis, search_axis_short) cells
+// smaller than R take exactly the one-thread walk's rows, larger ones pruned
+// rows in its order: `all` if it is one run from cell 0, its outer walls after
+// all of it (whole rows there: 6^3 boxes 2,000 at a time 549 us a step, pruned
+// 467; 20^3 in cells of 4 h 673 and 285).
 template <bool FP32, bool EXACT>
 __device__ __forceinline__ void search_row(const Geo& B, const Grid& G, int off, double px,
                                            double py, double pz, double R, const int cc[3], int kr,
                                            const StencilShape& sh, const PlainRows& p, int zi,
-                                           int yi, int& a0, int& a1, int& b0, int& b1) {
+                                           int yi, int& a0, int& a1, int& b0, int& b1,
+                                           bool& all) {
   const bool exact = EXACT && search_axis_short(G, B.le, kr);
-  if (exact && kr == 1)
-    stencil_row_zy<false>(B, G, off, px, py, pz, R, cc, 1, sh, sh.zlo + zi, sh.ylo + yi, a0, a1,
-                          b0, b1);
-  else if ((FP32 || exact) && p.plain)
+  all = false;
+  if ((FP32 || exact) && p.plain) {
     plain_row(p, G, off, cc, kr, zi - kr, yi - kr, a0, a1, b0, b1);
-  else
+    if (exact && kr == 1) {
+      all = true;  // without shear a short axis has 2 kr + 1 cells at most
+      if (b1 > b0) {
+        const int t0 = a0, t1 = a1;
+        a0 = b0;
+        a1 = b1;
+        b0 = t0;
+        b1 = t1;
+      }
+    }
+  } else if (exact && kr == 1) {
+    stencil_row_zy<true, true>(B, G, off, px, py, pz, R, cc, kr, sh, sh.zlo + zi, sh.ylo + yi, a0,
+                               a1, b0, b1, &all);
+  } else {
     stencil_row_zy<true>(B, G, off, px, py, pz, R, cc, kr, sh, sh.zlo + zi, sh.ylo + yi, a0, a1,
                          b0, b1);
+  }
 }
 
 // orders LDS accesses of the lanes of one wave (which run them in program

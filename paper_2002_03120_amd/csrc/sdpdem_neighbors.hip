@@ -236,16 +236,18 @@ __device__ __forceinline__ void build_density_wide(const Dev& d, int after_drift
     const unsigned below = (1u << g) - 1u;
     for (int rb = 0; rb < nrows; rb += G) {
       // row rb + g: up to two runs of consecutive cells, each followed by
-      // the outer walls binned in the same cells; s: first particle of a
-      // run, e: the run's end in the row
+      // the outer walls binned in the same cells (both first where they make
+      // one run of the one-lane walk); s: first particle of a run, e: the
+      // run's end in the row
       int s0 = 0, e0 = 0, s1 = 0, e1 = 0, s2 = 0, e2 = 0, s3 = 0, e3 = 0;
       if (rb + g < nrows) {
         int a0, a1, b0, b1;
+        bool all;
         // row / yn without an integer division: (row + 1/2) / yn stays at
         // least 1 / (2 yn) away from every integer
         const int zi = (int)(((float)(rb + g) + 0.5f) * inv_yn), yi = rb + g - zi * sh_.yn;
         search_row<!CAND, EXACT>(geo, gr, coff, pi.x, pi.y, pi.z, R, cc, kr, sh_, rows, zi, yi, a0,
-                                 a1, b0, b1);
+                                 a1, b0, b1, all);
         if (a1 > a0) {
           s0 = d.cstart[a0];
           e0 = d.cstart[a1] - s0;
@@ -261,6 +263,13 @@ __device__ __forceinline__ void build_density_wide(const Dev& d, int after_drift
             s3 = d.cstart[b0 + woff];
             e3 = d.cstart[b1 + woff] - s3;
           }
+        }
+        if (EXACT && all && woff) {
+          const int s = s1, e = e1;
+          s1 = s2;
+          e1 = e2;
+          s2 = s;
+          e2 = e;
         }
       }
       e1 += e0;

@@ -38,7 +38,7 @@ static void take(const Box& b, int i, double R, int c0, int c1, Fn&& fn) {
 template <bool FP32, bool EXACT>
 static int differing(const Box& b, double R) {
   int bad = 0;
-  const int kr = reach_cells(b.G, R);
+  const int kr = reach_cells(b.G, R), cells = b.G.nc[0] * b.G.nc[1] * b.G.nc[2];
   for (int i = 0; i < (int)b.x.size(); ++i) {
     const D4 p = b.x[i];
     int oob = 0;
@@ -57,10 +57,19 @@ static int differing(const Box& b, double R) {
     for (int zi = 0; zi < sh.zn; ++zi)
       for (int yi = 0; yi < sh.yn; ++yi) {
         int a0, a1, b0, b1;
+        bool all;
         search_row<FP32, EXACT>(b.B, b.G, 0, p.x, p.y, p.z, R, cc, kr, sh, rows, zi, yi, a0, a1,
-                                b0, b1);
-        if (a1 > a0) into(many, a0, a1);
-        if (b1 > b0) into(many, b0, b1);
+                                b0, b1, all);
+        if (all) {  // both runs, then the walls of both
+          const auto found = [&](int j) { many.push_back(j); };
+          for (int w = 0; w <= b.woff; w += cells) {
+            take(b, i, R, a0 + w, a1 + w, found);
+            take(b, i, R, b0 + w, b1 + w, found);
+          }
+        } else {
+          if (a1 > a0) into(many, a0, a1);
+          if (b1 > b0) into(many, b0, b1);
+        }
       }
     bad += one != many;
   }
